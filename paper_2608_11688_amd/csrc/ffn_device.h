@@ -43,10 +43,37 @@ __device__ __forceinline__ float dot8(uint4 w, float4 a, float4 b, float acc) {
     return acc;
 }
 
+// Cross-lane sums in the vector unit: rotations within rows of 16 lanes (DPP), then
+// exchanges of neighbouring rows and of the wavefront's halves.  Each step is one or two
+// vector instructions; through the LDS crossbar (__shfl_xor) it is a round trip of well
+// over a hundred cycles.
+template <int CTRL>
+__device__ __forceinline__ float row_ror(float v) {   // the value CTRL lanes further in the row
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float row_sum(float v) {   // over the row, in each of its lanes
+    v += row_ror<8>(v);
+    v += row_ror<4>(v);
+    v += row_ror<2>(v);
+    return v + row_ror<1>(v);
+}
+__device__ __forceinline__ float row_max(float v) {
+    v = fmaxf(v, row_ror<8>(v));
+    v = fmaxf(v, row_ror<4>(v));
+    v = fmaxf(v, row_ror<2>(v));
+    return fmaxf(v, row_ror<1>(v));
+}
+__device__ __forceinline__ float sum_xor16(float v) {   // v + the value of lane ^ 16
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float sum_xor32(float v) {   // v + the value of lane ^ 32
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+    return sum_xor32(sum_xor16(row_sum(v)));
 }
 
 __device__ __forceinline__ float silu(float u) { return u / (1.f + expf(-u)); }
