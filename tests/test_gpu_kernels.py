@@ -117,6 +117,25 @@ def test_route_edge_shapes(torch, d, E, k, k_max, tau):
         assert (cnt == min(E, k_max)).all()
 
 
+# every split of the router matrix over a workgroup: 1, 2, 4, 8 and 16 wavefronts along d
+# (128 values each; the last ones partly or wholly past d, and d of more than one pass), and
+# 1 to 8 groups of 4 experts per wavefront in one round and in two
+ROUTER_SHAPES = [(128, 64, 8), (136, 61, 4), (256, 5, 2), (264, 64, 6), (512, 17, 3), (520, 33, 8),
+                 (1024, 64, 8), (1032, 4, 2), (1160, 20, 5), (2048, 24, 4), (2056, 25, 6),
+                 (2176, 48, 8), (4104, 49, 7), (6152, 64, 8)]
+
+
+@pytest.mark.parametrize("d,E,k", ROUTER_SHAPES, ids=[f"d{d}-E{E}" for d, E, _ in ROUTER_SHAPES])
+def test_router_and_gate_shapes(torch, d, E, k):
+    cfg = shape(f"router{d}", 500 + E, d, E, k, bias=True)
+    ledger = check_route(torch, cfg, tokens(cfg, 33), native.SEL_CUMPROB, 0.9)
+    check_route(torch, cfg, tokens(cfg, 33), native.SEL_ORDINAL_CDF, 0.9,
+                cdf=inputs.cdf_params(cfg, 0), ledger=ledger)
+    avail = np.ones(E, np.uint8)
+    avail[::3] = 0
+    check_gate(torch, cfg, tokens(cfg, 33, which=1), native.MODE_STALL_FREE, avail, ledger=ledger)
+
+
 def test_route_writes_pinned_host_memory(torch):
     cfg = configs.GRANITE_1B
     h = tokens(cfg, 8)
