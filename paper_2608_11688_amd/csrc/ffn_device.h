@@ -72,8 +72,8 @@ __device__ __forceinline__ float sum_xor32(float v) {   // v + the value of lane
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-__device__ __forceinline__ float wave_sum(float v) {
-    return sum_xor32(sum_xor16(row_sum(v)));
+__device__ __forceinline__ float wave_sum(float v) {   // halves first, as a xor butterfly adds
+    return row_sum(sum_xor16(sum_xor32(v)));
 }
 
 __device__ __forceinline__ float silu(float u) { return u / (1.f + expf(-u)); }

@@ -6,8 +6,7 @@
 // (activations rounded to bf16, fp32 accumulation).  A workgroup owns 64 weight rows of
 // one expert (blockIdx.y is the expert id; experts without a slot exit at once) and
 // finds that expert's (token, position) pairs itself from exec_idx, in pair order, while
-// its first weight block loads (an expert without tokens then exits and drops that
-// block).  When a projection has too few row tiles to keep the chip's loads in flight
+// its first weight block loads into LDS (an expert without tokens then exits).  When a projection has too few row tiles to keep the chip's loads in flight
 // (plan_for), its K range is split over blockIdx.z and each split writes fp32 partial
 // sums:
 //   * up_gemm with one split writes h = bf16(silu(W1 x) * (W3 x)) per pair; with several
@@ -17,9 +16,9 @@
 //     gated positions of each token in a fixed order.
 // Slots hold bf16 weights (apex_pack_expert), E4M3 codes with fp32 row scales
 // (apex_pack_expert_fp8) or MXFP4 codes with a power-of-two scale per block of 32
-// (apex_pack_expert_mxfp4).  E4M3 and MXFP4 codes are staged in LDS as bytes and widened
-// to bf16 exactly at fragment read (MXFP4 with its block scales applied); the E4M3 row
-// scales multiply the outputs.  Every executed expert's weights are read once per call
+// (apex_pack_expert_mxfp4).  Weights go from memory to LDS as they are stored; E4M3 and
+// MXFP4 codes are widened to bf16 exactly at fragment read (MXFP4 with its block scales
+// applied); the E4M3 row scales multiply the outputs.  Every executed expert's weights are read once per call
 // whatever the number of tokens routed to it, and no atomics are used, so results are
 // deterministic.
 #include <hip/hip_runtime.h>
@@ -32,7 +31,6 @@
 namespace {
 
 using apex::ffn::kWave;
-using apex::ffn::ld_stream;
 using apex::ffn::silu;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -40,8 +38,6 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
 constexpr int kRows = 64;          // weight rows per workgroup tile
-constexpr int kKB = 128;           // K per staged block
-constexpr int kLdsRow = kKB + 8;   // +16 B per row: the 16 rows of a fragment read hit distinct banks
 constexpr int kMaxSplit = 4;
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -65,6 +61,7 @@ __device__ __forceinline__ uint4 keep_if(uint4 v, bool c) {
 // arithmetic follows a load directly (which would make the compiler wait for it, and for
 // every older load, before the matrix cores work on the previous block).
 struct ActF32 {          // fp32 rows (the FFN input x), rounded to bf16 at staging
+    static constexpr int kLoads = 2;
     struct Raw {
         float4 a, b;
     };
@@ -77,6 +74,7 @@ struct ActF32 {          // fp32 rows (the FFN input x), rounded to bf16 at stag
     }
 };
 struct ActBf16 {         // bf16 rows (h)
+    static constexpr int kLoads = 1;
     using Raw = uint4;
     static __device__ __forceinline__ Raw load(const void *row, int kc) {
         return *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(row) + kc);
@@ -109,34 +107,25 @@ __device__ __forceinline__ uint4 swiglu8(const float *r, size_t stride) {
 // kUpGroups: workgroups the gate/up projection's K splits aim at (see plan_for);
 // kKPerElem: K values per element of T; kFp8: fp32 row scales after the codes;
 // kBlockScale: one scale byte per 32 K values of a row;
-// kCodes: the codes go to LDS as bytes, in K blocks of kb<MT>() values, and are widened
-// at fragment read; otherwise bf16 tiles of kKB,
-// where one 16-byte load covers 8 K values of a row, kThrPerRow threads cover a block of
-// the row and kRowsPerPass rows are loaded per pass of the workgroup.
+// kChunkK: K values in 16 bytes of a row; plan_kb<MT>(): K values that the split rule
+// counts as one block.
 struct WBf16 {           // apex_pack_expert slots: bf16 weights
     using T = uint16_t;
-    [[maybe_unused]] static constexpr bool kFp8 = false, kBlockScale = false, kCodes = false;
-    template <int MT> static constexpr int kb() { return kKB; }
-    static constexpr int kUpGroups = 400;
-    static constexpr int kKPerElem = 1;
-    static constexpr int kThrPerRow = kKB / 8, kRowsPerPass = kThreads / kThrPerRow;
-    static constexpr int kLoads = kRows / kRowsPerPass;
+    static constexpr bool kFp8 = false, kBlockScale = false;
+    template <int MT> static constexpr int plan_kb() { return 128; }
+    static constexpr int kUpGroups = 400, kKPerElem = 1, kChunkK = 8;
 };
 struct WE4M3 {           // apex_pack_expert_fp8 slots: E4M3 codes, fp32 row scales after them
     using T = uint8_t;
-    static constexpr bool kFp8 = true, kBlockScale = false, kCodes = true;
-    // 256 bytes per row with one token tile, 128 with more (a smaller activation tile)
-    template <int MT> static constexpr int kb() { return MT == 1 ? 256 : 128; }
-    static constexpr int kUpGroups = 800;
-    static constexpr int kKPerElem = 1;
+    static constexpr bool kFp8 = true, kBlockScale = false;
+    template <int MT> static constexpr int plan_kb() { return MT == 1 ? 256 : 128; }
+    static constexpr int kUpGroups = 800, kKPerElem = 1, kChunkK = 16;
 };
 struct WMxfp4 {          // apex_pack_expert_mxfp4 slots: two E2M1 codes per byte, block scales
     using T = uint8_t;
-    static constexpr bool kFp8 = false, kBlockScale = true, kCodes = true;
-    // 256 bytes per row with one token tile, 128 with more (a smaller activation tile)
-    template <int MT> static constexpr int kb() { return MT == 1 ? 512 : 256; }
-    static constexpr int kUpGroups = 1400;
-    static constexpr int kKPerElem = 2;
+    static constexpr bool kFp8 = false, kBlockScale = true;
+    template <int MT> static constexpr int plan_kb() { return MT == 1 ? 512 : 256; }
+    static constexpr int kUpGroups = 1400, kKPerElem = 2, kChunkK = 32;
 };
 
 constexpr int kPairRounds = APEX_MAX_PAIRS / kThreads;
@@ -149,13 +138,19 @@ __device__ __forceinline__ void pair_ids(const int32_t *__restrict__ exec_idx, i
 #pragma unroll
     for (int r = 0; r < kPairRounds; ++r) {
         const int p = r * kThreads + threadIdx.x;
-        ev[r] = exec_idx[p < P ? p : P - 1];
+        ev[r] = r == 0 || r * kThreads < P ? exec_idx[p < P ? p : P - 1] : -1;
     }
+}
+
+// A workgroup barrier that leaves global loads in flight (__syncthreads would wait for the
+// loads into LDS): this wavefront's LDS operations are done, then the others' are.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // The pairs p < P with exec_idx[p] == e, in ascending order, into list[]; returns how
 // many.  256 threads; P <= 1024 (four rounds of wave ballots).
-__device__ int expert_pairs(const int (&ev)[kPairRounds], int P, int e, int *list,
+__device__ int expert_pairs(const int (&ev)[kPairRounds], int P, int e, uint16_t *list,
                             int (*cnt)[4]) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     bool hit[kPairRounds];
@@ -166,16 +161,17 @@ __device__ int expert_pairs(const int (&ev)[kPairRounds], int P, int e, int *lis
         m[r] = __ballot(hit[r]);
         if (lane == 0) cnt[r][wave] = __popcll(m[r]);
     }
-    __syncthreads();
+    lds_barrier();
     int base = 0;
 #pragma unroll
     for (int r = 0; r < kPairRounds; ++r) {
+        if (r * kThreads >= P) break;
         int off = base;
         for (int w = 0; w < wave; ++w) off += cnt[r][w];
-        if (hit[r]) list[off + __popcll(m[r] & ((1ull << lane) - 1ull))] = r * kThreads + t;
+        if (hit[r]) list[off + __popcll(m[r] & ((1ull << lane) - 1ull))] = uint16_t(r * kThreads + t);
         base += cnt[r][0] + cnt[r][1] + cnt[r][2] + cnt[r][3];
     }
-    __syncthreads();
+    lds_barrier();
     return base;
 }
 
@@ -201,221 +197,271 @@ __device__ __forceinline__ KBlocks k_blocks(int K, int kb, int splits, int z) {
     return r;
 }
 
-// LDS of one workgroup's tile: bf16 weights and activations for bf16 slots; codes, MXFP4
-// block scales and activations for the compact formats.  Rows are padded by 16
-// bytes so that the 16 rows of a fragment read fall in distinct banks.
-template <int NW, int MT, class WF, bool C = WF::kCodes>
-struct GemmLds {
-    uint16_t Ws[NW][kRows][kLdsRow];
-    uint16_t Xs[16 * MT][kLdsRow];
-};
+__device__ __forceinline__ uint4 widen8(WBf16, uint4 v, int, float) { return v; }
+// 8 of a chunk's codes (the j-th eighth of 8) widened to bf16 exactly: E4M3 values are bf16
+// values; an E2M1 value times its power-of-two scale too.
+__device__ __forceinline__ uint4 widen8(WE4M3, uint4 v, int j, float) {
+    const int c0 = int(j ? v.z : v.x), c1 = int(j ? v.w : v.y);
+    const auto a = __builtin_amdgcn_cvt_pk_f32_fp8(c0, false);
+    const auto b = __builtin_amdgcn_cvt_pk_f32_fp8(c0, true);
+    const auto e = __builtin_amdgcn_cvt_pk_f32_fp8(c1, false);
+    const auto f = __builtin_amdgcn_cvt_pk_f32_fp8(c1, true);
+    const auto pk = [](float lo, float hi) {
+        return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+    };
+    return make_uint4(pk(a[0], a[1]), pk(b[0], b[1]), pk(e[0], e[1]), pk(f[0], f[1]));
+}
+__device__ __forceinline__ uint4 widen8(WMxfp4, uint4 v, int j, float sc) {
+    const uint32_t c = j == 0 ? v.x : j == 1 ? v.y : j == 2 ? v.z : v.w;
+    return make_uint4(
+        __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c, sc, 0)),
+        __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c, sc, 1)),
+        __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c, sc, 2)),
+        __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c, sc, 3)));
+}
+
+// Sizes of one workgroup's tile: NW matrices of 64 rows, up to 16 * MT tokens, K in blocks
+// of KB values (one or two cache lines of every weight row).  D weight stages are in LDS, the
+// loads of D - 1 blocks on the way or done while one is multiplied; the activations of the
+// next PX blocks are in registers or on the way.
+// D: more stages hide more of a load's time, fewer let more workgroups share a CU's 160 KB,
+// which hides the start of a workgroup (slot, pair scan, first activations) and evens out
+// the last wave of them.  Measured, us a launch: gate/up of 64 tokens, bf16 (OLMoE) D = 2
+// 49.6, 3 37.8, 4 45.7; MXFP4, 16 tokens (DeepSeek-16B) D = 2 26.0, 3 35.1, 4 37.1; down of
+// 64 tokens, bf16 D = 2 23.0, 4 21.5, 6 28.4; E4M3, 32 tokens (Mixtral) D = 2 43.9, 4 54.2;
+// MXFP4, 16 tokens D = 2 16.2, 4 17.4.
+// Two lines per row and block halve the barriers: for up to 16 tokens and bf16, whose blocks
+// have the least work (Granite-3B, 8 tokens: gate/up 14.2 -> 13.2, down 11.0 -> 9.5 us); with
+// more tokens or codes the larger activation tile costs more than that (down: OLMoE 21.5 ->
+// 25.4, Mixtral E4M3 43.9 -> 48.5, DeepSeek-16B MXFP4 16.2 -> 19.6).
+// Before (weights through registers to LDS, one block ahead, two barriers a block, all MT
+// token tiles multiplied; us a launch, up / down): OLMoE 45.9 / 25.2, Granite-3B 15.2 / 10.6,
+// DeepSeek-16B MXFP4 29.3 / 14.9, Mixtral E4M3 92.7 / 60.7; now 37.8 / 21.5, 13.2 / 9.5,
+// 25.9 / 16.1, 96.4 / 43.9.  A bare stream of the same bytes through LDS takes 34.5 / 16.1,
+// 11.2 / 5.7, 13.7 / -, 78.9 / 35.5.
 template <int NW, int MT, class WF>
-struct GemmLds<NW, MT, WF, true> {
-    static constexpr int KB = WF::template kb<MT>();   // K values per block
-    static constexpr int RB = KB / WF::kKPerElem;      // code bytes per row and block
-    uint8_t Wc[NW][kRows][RB + 16];
-    uint8_t Sc[NW][kRows][KB / 32];                    // MXFP4 block scales
-    uint16_t Xs[16 * MT][KB + 8];
+struct TileShape {
+    static constexpr bool kWide = WF::kChunkK == 8 && MT == 1;
+    static constexpr int kRowBytes = kWide ? 256 : 128;   // of a weight row per block
+    static constexpr int kChunks = kRowBytes / 16;
+    static constexpr int KB = kChunks * WF::kChunkK;
+    static constexpr int kStage = NW * kRows * kRowBytes;
+    static constexpr int kXRow = KB + 8;   // +16 B: the 16 rows of a fragment read hit distinct banks
+    static constexpr int kXs = 16 * MT * kXRow * 2;
+    static constexpr bool kMx = WF::kChunkK == 32;   // twice the activations of E4M3 per block
+    static constexpr int D = NW == 1   ? (MT == 4 || WF::kChunkK == 8 ? 4 : 2)
+                             : MT == 4 ? (kMx ? 2 : 3)
+                             : MT == 2 ? (kMx ? 3 : 4)
+                                       : 2;
+    static constexpr int PX = D == 4 ? 2 : 1;
+    static constexpr int kList = APEX_MAX_PAIRS * 2 + kPairRounds * 16 + 64;
+    // activation buffers: two take a barrier per block, one takes two
+    static constexpr int XB = D == 3 || D * kStage + 2 * kXs + kList > 80 * 1024 ? 1 : 2;
+    static constexpr int kLds = D * kStage + XB * kXs + kList;
+    static constexpr int UN = D;   // blocks per unrolled round: a multiple of D and of PX
+    static_assert(kLds <= 80 * 1024 && UN % D == 0 && UN % PX == 0 && (XB == 1 || UN % 2 == 0), "tile");
 };
 
-// 8 consecutive codes of row rr at K offset kc of the staged block, widened to bf16
-// exactly (E4M3 values are bf16 values; an E2M1 value times its power-of-two scale too).
-template <int NW, int MT, class WF>
-__device__ __forceinline__ uint4 widen8(const GemmLds<NW, MT, WF, true> &lds, int m, int rr,
-                                        int kc) {
-    if constexpr (WF::kBlockScale) {
-        const uint32_t c = *reinterpret_cast<const uint32_t *>(&lds.Wc[m][rr][kc / 2]);
-        const float sc = apex::ffn::mx_scale(lds.Sc[m][rr][kc / 32]);
-        return make_uint4(
-            __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c, sc, 0)),
-            __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c, sc, 1)),
-            __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c, sc, 2)),
-            __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c, sc, 3)));
-    } else {
-        const uint2 c = *reinterpret_cast<const uint2 *>(&lds.Wc[m][rr][kc]);
-        const auto a = __builtin_amdgcn_cvt_pk_f32_fp8(int(c.x), false);
-        const auto b = __builtin_amdgcn_cvt_pk_f32_fp8(int(c.x), true);
-        const auto e = __builtin_amdgcn_cvt_pk_f32_fp8(int(c.y), false);
-        const auto f = __builtin_amdgcn_cvt_pk_f32_fp8(int(c.y), true);
-        const auto pk = [](float lo, float hi) {
-            return (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xffff0000u);
-        };
-        return make_uint4(pk(a[0], a[1]), pk(b[0], b[1]), pk(e[0], e[1]), pk(f[0], f[1]));
+template <int I>
+struct Int {
+    static constexpr int value = I;
+};
+
+// The permutation of a row's 16-byte chunks in LDS: the 16 rows of a fragment read, at the
+// same chunk, then fall in distinct banks.
+template <int RB>
+__device__ __forceinline__ int swizzle(int row) {
+    return RB == 256 ? row & 15 : row >> 1;
+}
+
+// The s_waitcnt operand that waits until at most n (capped) vector loads are outstanding.
+constexpr int vmcnt_only(int n) {
+    n = n > 63 ? 63 : n;
+    return 0x0f70 | (n & 15) | (n >> 4 << 14);
+}
+
+// The weights of block b (16 rows per wavefront and matrix) into a stage; a block past the
+// last one loads nothing (offsets past the buffer's end).  Buffer loads: the compiler takes
+// global loads into LDS for accesses of either memory and waits for all of them at the
+// next use of any loaded register.
+template <int NW, int RB, class WF>
+__device__ __forceinline__ void load_weights(uint8_t *st, const uint8_t *const (&wbase)[NW],
+                                             size_t wstride, int rows_valid, int K,
+                                             const KBlocks &kr, int b) {
+    constexpr int CH = RB / 16, RPI = kWave / CH;   // chunks of a row, rows per instruction
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int k0 = kr.k0(min(b, kr.nb > 0 ? kr.nb - 1 : 0));
+    const int row0 = min(16 * wave, rows_valid - 1);   // rows past the tile's last repeat it
+#pragma unroll
+    for (int m = 0; m < NW; ++m) {
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint8_t *>(wbase[m]) + size_t(row0) * wstride, 0,
+            b < kr.nb ? 0xffffffffu : 0u, 0x00027000);
+#pragma unroll
+        for (int i = 0; i < 16 / RPI; ++i) {
+            const int row = RPI * i + lane / CH;             // of the wavefront's 16
+            const int chunk = (lane % CH) ^ swizzle<RB>(row);
+            const int k = min(k0 + chunk * WF::kChunkK, K - WF::kChunkK);
+            const uint32_t at = uint32_t(min(row, rows_valid - 1 - row0)) * uint32_t(wstride) +
+                                uint32_t(k) / WF::kChunkK * 16u;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rsrc,
+                (__attribute__((address_space(3))) void *)(st + ((wave * NW + m) * 16 + RPI * i) * RB),
+                16, at, 0, 0, 2 /* non-temporal */);
+        }
     }
 }
 
-// One K block of a tile's weights in registers: every address valid (rows and K
-// clamped), pieces outside the tile zeroed when the block is staged in LDS, not when it
-// arrives, so that the loads stay in flight until then.
-// bf16 slots: 16 threads per 256-byte piece of a row, 16 rows per pass of 256 threads.
-template <int NW, int MT, class WF, bool C = WF::kCodes>
-struct WRegs {
-    static constexpr int kLoads = WBf16::kLoads, kRpp = WBf16::kRowsPerPass,
-                         kTpr = WBf16::kThrPerRow;
-    uint4 v[NW][kLoads];
-    bool in = false;
-    __device__ __forceinline__ void load(const uint16_t *const (&wbase)[NW], size_t wstride,
-                                         const uint8_t *const (&)[NW], size_t, int rows_valid,
-                                         int K, int k0) {
-        const int t = threadIdx.x, wseg = t % kTpr, wr0 = t / kTpr;
-        const int wk = k0 + 8 * wseg;
-        in = wk < K;
-        const int wkc = in ? wk : K - 8;
-#pragma unroll
-        for (int m = 0; m < NW; ++m)
-#pragma unroll
-            for (int j = 0; j < kLoads; ++j) {
-                const int row = wr0 + kRpp * j;
-                const int rc = row < rows_valid ? row : rows_valid - 1;
-                v[m][j] = ld_stream(
-                    reinterpret_cast<const uint4 *>(wbase[m] + size_t(rc) * wstride + wkc));
-            }
-    }
-    __device__ __forceinline__ void stage(GemmLds<NW, MT, WF> &lds, int rows_valid) const {
-        const int t = threadIdx.x, wseg = t % kTpr, wr0 = t / kTpr;
-#pragma unroll
-        for (int m = 0; m < NW; ++m)
-#pragma unroll
-            for (int j = 0; j < kLoads; ++j) {
-                const int row = wr0 + kRpp * j;
-                *reinterpret_cast<uint4 *>(&lds.Ws[m][row][8 * wseg]) =
-                    keep_if(v[m][j], in && row < rows_valid);
-            }
-    }
-};
-
-// E4M3 and MXFP4 slots: the codes (and MXFP4 block scales) as stored, RB bytes per row
-// and block.
-template <int NW, int MT, class WF>
-struct WRegs<NW, MT, WF, true> {
-    using L = GemmLds<NW, MT, WF, true>;
-    static constexpr int TPR = L::RB / 16;          // threads per row of a block
-    static constexpr int RPP = kThreads / TPR;      // rows per pass
-    static constexpr int NL = kRows / RPP;          // 16-byte loads per thread and matrix
-    static constexpr int KPL = 16 * WF::kKPerElem;  // K values per 16-byte load
-    uint4 v[NW][NL];
-    uint32_t sc[NW][NL];
-    bool in = false;
-    __device__ __forceinline__ void load(const uint8_t *const (&wbase)[NW], size_t wstride,
-                                         const uint8_t *const (&sbase)[NW], size_t sstride,
-                                         int rows_valid, int K, int k0) {
-        const int t = threadIdx.x, wseg = t % TPR, wr0 = t / TPR;
-        const int wk = k0 + KPL * wseg;
-        in = wk < K;
-        const int wkc = in ? wk : K - KPL;
-#pragma unroll
-        for (int m = 0; m < NW; ++m)
-#pragma unroll
-            for (int j = 0; j < NL; ++j) {
-                const int row = wr0 + RPP * j;
-                const int rc = row < rows_valid ? row : rows_valid - 1;
-                v[m][j] = ld_stream(reinterpret_cast<const uint4 *>(
-                    wbase[m] + size_t(rc) * wstride + wkc / WF::kKPerElem));
-                if constexpr (WF::kBlockScale) sc[m][j] = sbase[m][size_t(rc) * sstride + wkc / 32];
-            }
-    }
-    __device__ __forceinline__ void stage(L &lds, int rows_valid) const {
-        const int t = threadIdx.x, wseg = t % TPR, wr0 = t / TPR;
-#pragma unroll
-        for (int m = 0; m < NW; ++m)
-#pragma unroll
-            for (int j = 0; j < NL; ++j) {
-                const int row = wr0 + RPP * j;
-                *reinterpret_cast<uint4 *>(&lds.Wc[m][row][16 * wseg]) =
-                    keep_if(v[m][j], in && row < rows_valid);
-                if constexpr (WF::kBlockScale) lds.Sc[m][row][wseg] = uint8_t(sc[m][j]);
-            }
-    }
-};
-
 // Grouped-GEMM mainloop, shared by the gate/up and down projections and the weight
 // formats.  A workgroup (4 wavefronts) owns a tile of 64 weight rows of NW weight
-// matrices and up to 16*MT tokens, over the K blocks of kr.  Every thread loads 16-byte
-// pieces so that each group of threads reads whole cache lines of one weight row, the
-// block goes to LDS, and while the matrix cores work on it the next block is already
-// loading into registers: every load address is valid (padding token rows read a real
-// row), and zeroing and the fp32-to-bf16 conversion of activations happen at staging,
-// so the first use of a loaded register comes after the matrix-core work on the previous
-// block.  `w` may already hold the first block (w_ready): the kernels issue it before
-// they look up the expert's pairs.
-// bf16 slots: K blocks of kKB values as bf16 tiles.  E4M3 and MXFP4 slots: a block holds
-// as many code bytes per row as a bf16 block (256 or 512 K values with one token tile,
-// 128 or 256 with more), the codes go to LDS unchanged (the MXFP4 block scales beside
-// them), and each wavefront widens its own fragments right before the matrix cores take
-// them: every code is converted once, the bytes in flight per block match bf16, and the
-// LDS moves a fraction of the widened data.
-// Wavefront w multiplies its 16 rows with every token tile: v_mfma_f32_16x16x32_bf16,
-// tokens as M, weight rows as N.  Tiles past the expert's last token multiply zero rows:
-// skipping them on the token count made the compiler move the accumulators between
-// register files around the skip, and the E4M3 kernel with two tiles then gave wrong
-// sums that changed from run to run.
-template <int NW, int MT, class Act, class WF>
-__device__ __forceinline__ void gemm_tile(WRegs<NW, MT, WF> &w, bool w_ready,
-                                          const typename WF::T *const (&wbase)[NW],
-                                          size_t wstride, const uint8_t *const (&sbase)[NW],
-                                          size_t sstride, int rows_valid, int K,
-                                          const KBlocks &kr, const void *const (&xrow)[MT],
-                                          const bool (&xok)[MT], GemmLds<NW, MT, WF> &lds,
-                                          floatx4 (&acc)[NW][MT]) {
-    constexpr int KB = WF::template kb<MT>();
-    constexpr int QX = KB / 128;   // 8-value activation pieces per token row and thread
+// matrices and up to 16 * NT tokens, over the K blocks of kr.
+//
+// Weights go from memory to LDS directly (16 bytes per lane, 8 rows of 128 bytes or 4 of 256
+// per instruction), each wavefront loading the 16 rows that it multiplies: no barrier and no
+// register stands between a weight load and its use, only the wavefront's own count of
+// loads.  A row's chunks are permuted (by the lanes' addresses, the LDS side being linear)
+// so that the 16 rows of a fragment read fall in distinct banks.  Codes stay codes in LDS
+// and are widened to bf16 right before the matrix cores take them.  A lane multiplies the
+// K values of its own chunks: the activations are read in the same order.
+// Activations are the same for all four wavefronts: loaded PX blocks ahead into registers,
+// converted to bf16 and staged in LDS, with a barrier per block (two with one buffer).
+// Loads return in order, so a wait for activations is also one for the weights requested
+// before them: PX blocks of weights stay in flight across it.
+// Every load is unconditional (blocks past the last one read one cached line, rows past
+// the last one that row) so that the compiler's load counts are exact.  K past the end is
+// zero on both sides; rows and tokens past the end are multiplied and dropped.
+template <int NW, int MT, int NT, class Act, class WF, class Stage>
+__device__ __forceinline__ void gemm_tile(const Stage &stage, uint16_t *xs, bool w_ready,
+                                          const uint8_t *const (&wbase)[NW], size_t wstride,
+                                          const uint8_t *const (&sbase)[NW], size_t sstride,
+                                          int rows_valid, int K, const KBlocks &kr,
+                                          const uint16_t *list, int n_tok, int list_div,
+                                          const void *act, size_t act_stride,
+                                          floatx4 (&acc)[NW][NT]) {
+    using S = TileShape<NW, MT, WF>;
+    constexpr int KB = S::KB, D = S::D, PX = S::PX;
+    constexpr int SPR = KB / 8;                                    // 8-value pieces per token
+    constexpr int XP = 16 * NT * SPR / kThreads > 0 ? 16 * NT * SPR / kThreads : 1;
+    constexpr int P = S::kChunks / 4, SUB = WF::kChunkK / 8;          // matrix-core steps
     const int t = threadIdx.x, wave = t / kWave, lane = t % kWave;
-    const int seg = t & 15, r0 = t >> 4;
-    typename Act::Raw xraw[QX][MT];
-    bool x_in[QX];
+    const int n = lane & 15, g = lane >> 4;
+    // activation pieces of this thread (threads past the last piece repeat others')
+    const uint8_t *xrow[XP];
+    int xk[XP], xat[XP];
+#pragma unroll
+    for (int j = 0; j < XP; ++j) {
+        const int p = (t + j * kThreads) % (16 * NT * SPR);
+        const int row = p / SPR;
+        xk[j] = 8 * (p % SPR);
+        xat[j] = row * S::kXRow + xk[j];
+        xrow[j] = static_cast<const uint8_t *>(act) +
+                  list[row < n_tok ? row : 0] / list_div * act_stride;
+    }
+    // Loads that may still be on the way when block b is multiplied: those requested after
+    // its weights, in the steady state and behind the first blocks.  (The compiler does not
+    // tie a load into LDS to the reads of it.)  Waiting for the activations of block b
+    // covers this already where PX < D - 1.
+    constexpr int kXLoads = XP * Act::kLoads + (WF::kBlockScale ? NW * P : 0), kWLoads = NW * S::kRowBytes / 64;
+    constexpr int kInFlight = std::min((D - 1) * (kXLoads + kWLoads),
+                                       (D - 1) * kWLoads + (PX + 1) * kXLoads);
+    typename Act::Raw xraw[PX][XP];
+    float sc[PX][NW][P];
 #pragma unroll
     for (int m = 0; m < NW; ++m)
 #pragma unroll
-        for (int tt = 0; tt < MT; ++tt) acc[m][tt] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int tt = 0; tt < NT; ++tt) acc[m][tt] = floatx4{0.f, 0.f, 0.f, 0.f};
     if (kr.nb <= 0) return;
-    const auto load_x = [&](int k0) {
+    const int row_c = min(16 * wave + n, rows_valid - 1);
+    const auto load_x = [&](int b, typename Act::Raw(&x)[XP], float(&scale)[NW][P]) {
+        const int k0 = kr.k0(min(b, kr.nb - 1));
 #pragma unroll
-        for (int q = 0; q < QX; ++q) {
-            const int kk = k0 + 128 * q + 8 * seg;
-            x_in[q] = kk < K;
-            const int kc = x_in[q] ? kk : K - 8;
+        for (int j = 0; j < XP; ++j) x[j] = Act::load(xrow[j], min(k0 + xk[j], K - 8));
+        if constexpr (WF::kBlockScale)
 #pragma unroll
-            for (int j = 0; j < MT; ++j) xraw[q][j] = Act::load(xrow[j], kc);
+            for (int m = 0; m < NW; ++m)
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+                    scale[m][p] = __uint_as_float(
+                        sbase[m][size_t(row_c) * sstride + min(k0 / 32 + 4 * p + g, K / 32 - 1)]);
+    };
+    const auto block = [&](auto which, int b) {
+        constexpr int I = decltype(which)::value;
+        auto &x = xraw[I % PX];
+        uint16_t *xb = xs + (S::XB == 2 ? (I & 1) * (16 * MT * S::kXRow) : 0);
+        const int end = b < kr.nb ? K : 0;   // a block past the last one multiplies zeros
+        const int k0 = kr.k0(min(b, kr.nb - 1));
+        if (S::XB == 1) lds_barrier();   // the previous block's activations have been read
+#pragma unroll
+        for (int j = 0; j < XP; ++j)
+            *reinterpret_cast<uint4 *>(xb + xat[j]) = keep_if(Act::to_bf16(x[j]), k0 + xk[j] < end);
+        float scale[NW][P];
+#pragma unroll
+        for (int m = 0; m < NW; ++m)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                scale[m][p] = WF::kBlockScale
+                                  ? apex::ffn::mx_scale(__float_as_uint(sc[I % PX][m][p])) : 1.f;
+        lds_barrier();
+        load_x(b + PX, x, sc[I % PX]);
+        load_weights<NW, S::kRowBytes, WF>(stage(Int<(I + D - 1) % D>{}), wbase, wstride, rows_valid, K, kr,
+                             b + D - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(vmcnt_only(kInFlight));   // block b's weights are in LDS
+        asm volatile("" ::: "memory");
+        const uint8_t *w = stage(Int<I % D>{}) + wave * (NW * 16 * S::kRowBytes);
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            uint4 raw[NW];
+#pragma unroll
+            for (int m = 0; m < NW; ++m)
+                raw[m] = *reinterpret_cast<const uint4 *>(
+                    w + (m * 16 + n) * S::kRowBytes + 16 * ((4 * p + g) ^ swizzle<S::kRowBytes>(n)));
+#pragma unroll
+            for (int m = 0; m < NW; ++m)
+                raw[m] = keep_if(raw[m], k0 + (4 * p + g) * WF::kChunkK < end);
+#pragma unroll
+            for (int j = 0; j < SUB; ++j) {
+                uint4 wop[NW];
+#pragma unroll
+                for (int m = 0; m < NW; ++m) wop[m] = widen8(WF{}, raw[m], j, scale[m][p]);
+#pragma unroll
+                for (int tt = 0; tt < NT; ++tt) {
+                    const uint4 xop = *reinterpret_cast<const uint4 *>(
+                        xb + (16 * tt + n) * S::kXRow + 8 * ((4 * p + g) * SUB + j));
+#pragma unroll
+                    for (int m = 0; m < NW; ++m)
+                        acc[m][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            as_bf16x8(xop), as_bf16x8(wop[m]), acc[m][tt], 0, 0, 0);
+                }
+            }
         }
     };
-    if (!w_ready) w.load(wbase, wstride, sbase, sstride, rows_valid, K, kr.k0(0));
-    load_x(kr.k0(0));
-    for (int b = 0; b < kr.nb; ++b) {
-        __syncthreads();   // the previous block's fragments have been read
-        w.stage(lds, rows_valid);
-#pragma unroll
-        for (int q = 0; q < QX; ++q)
-#pragma unroll
-            for (int j = 0; j < MT; ++j)
-                *reinterpret_cast<uint4 *>(&lds.Xs[r0 + 16 * j][128 * q + 8 * seg]) =
-                    keep_if(Act::to_bf16(xraw[q][j]), x_in[q] && xok[j]);
-        __syncthreads();
-        if (b + 1 < kr.nb) {
-            w.load(wbase, wstride, sbase, sstride, rows_valid, K, kr.k0(b + 1));
-            load_x(kr.k0(b + 1));
-        }
-        const int rr = 16 * wave + (lane & 15);
-#pragma unroll 4
-        for (int q = 0; q < KB / 32; ++q) {
-            const int kc = 32 * q + 8 * (lane >> 4);
-            uint4 wop[NW];
-#pragma unroll
-            for (int m = 0; m < NW; ++m) {
-                if constexpr (WF::kCodes)
-                    wop[m] = widen8(lds, m, rr, kc);
-                else
-                    wop[m] = *reinterpret_cast<const uint4 *>(&lds.Ws[m][rr][kc]);
+    // the requests ahead of the first block in the order of the later ones, so that the
+    // compiler's count of loads at the top of the loop is the same on both ways into it
+    const auto ahead = [&](auto which) {   // iteration I - (D - 1)
+        constexpr int I = decltype(which)::value;
+        if constexpr (I < D - 1) {
+            if constexpr (I >= D - 1 - PX) {
+                load_x(I - (D - 1 - PX), xraw[I - (D - 1 - PX)], sc[I - (D - 1 - PX)]);
+                __builtin_amdgcn_sched_barrier(0);
             }
-#pragma unroll
-            for (int tt = 0; tt < MT; ++tt) {
-                const uint4 xop = *reinterpret_cast<const uint4 *>(&lds.Xs[16 * tt + (lane & 15)][kc]);
-#pragma unroll
-                for (int m = 0; m < NW; ++m)
-                    acc[m][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        as_bf16x8(xop), as_bf16x8(wop[m]), acc[m][tt], 0, 0, 0);
-            }
+            if (I > 0 || !w_ready)
+                load_weights<NW, S::kRowBytes, WF>(stage(Int<I>{}), wbase, wstride, rows_valid, K, kr, I);
+            __builtin_amdgcn_sched_barrier(0);
         }
+    };
+    ahead(Int<0>{});
+    ahead(Int<1>{});
+    ahead(Int<2>{});
+    for (int b = 0; b < kr.nb; b += S::UN) {
+        block(Int<0>{}, b);
+        block(Int<1>{}, b + 1);
+        if constexpr (S::UN > 2) block(Int<2>{}, b + 2);
+        if constexpr (S::UN > 3) block(Int<3>{}, b + 3);
     }
+    // no load into LDS may outlive its stage (the next pass or another workgroup's LDS)
+    __builtin_amdgcn_s_waitcnt(0x0f70);
 }
 
 // The fp32 row scales of an apex_pack_expert_fp8 slot: W1 rows, W3 rows, W2 rows.
@@ -424,6 +470,21 @@ __device__ __forceinline__ const float *row_scales(const typename WF::T *slot, i
     return reinterpret_cast<const float *>(slot + size_t(3) * I * d);
 }
 
+// The stages of a tile: LDS arrays of their own, so that the compiler tells a load into one
+// from a read of another.
+#define APEX_STAGES(NW_)                                                                       \
+    using S = TileShape<NW_, MT, WF>;                                                          \
+    __shared__ __align__(16) uint8_t st0[S::kStage], st1[S::kStage];                           \
+    __shared__ __align__(16) uint8_t st2[S::D > 2 ? S::kStage : 16];                           \
+    __shared__ __align__(16) uint8_t st3[S::D > 3 ? S::kStage : 16];                           \
+    __shared__ __align__(16) uint16_t xs[S::XB * S::kXs / 2];                                  \
+    __shared__ uint16_t list[APEX_MAX_PAIRS];                                                  \
+    __shared__ int cnt[kPairRounds][4];                                                        \
+    const auto stage = [&](auto i) -> uint8_t * {                                              \
+        constexpr int I = decltype(i)::value;                                                  \
+        return I == 0 ? st0 : I == 1 ? st1 : I == 2 ? st2 : st3;                               \
+    };
+
 // up_gemm: grid (ceil(I / 64), E, SU).  64 rows of W1 and W3 of expert blockIdx.y, every
 // token of the expert (16*MT per pass), K blocks of split blockIdx.z.  slot_stride is
 // the slot size in elements of WF::T.
@@ -431,49 +492,39 @@ __device__ __forceinline__ const float *row_scales(const typename WF::T *slot, i
 // SU  > 1: uv[(2z) * P*I + pair*I + i] = W1[i] . x_b over the split, uv[(2z+1) ...] = W3.
 // E4M3 slots: the dot products are multiplied by the rows' scales.
 template <int MT, int SU, class WF>
-__global__ __launch_bounds__(kThreads) void up_gemm(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void up_gemm(
     const float *__restrict__ x, int d, int I, int P, int k, const int32_t *__restrict__ exec_idx,
     const int32_t *__restrict__ slot_of_expert, int n_slots,
     const typename WF::T *__restrict__ slots, size_t slot_stride, __bf16 *__restrict__ hb,
     float *__restrict__ uv) {
-    __shared__ __align__(16) GemmLds<2, MT, WF> lds;
-    __shared__ int list[APEX_MAX_PAIRS];
-    __shared__ int cnt[kPairRounds][4];
+    APEX_STAGES(2)
     const int e = blockIdx.y;
-    const int s = slot_of_expert[e];
-    if (s < 0 || s >= n_slots) return;
     int ev[kPairRounds];
     pair_ids(exec_idx, P, ev);
+    const int s = slot_of_expert[e];
+    if (s < 0 || s >= n_slots) return;
     const int i0 = blockIdx.x * kRows;
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const typename WF::T *slot = slots + size_t(s) * slot_stride;
-    const typename WF::T *W = slot + size_t(i0) * 2 * d / WF::kKPerElem;
-    const typename WF::T *const wbase[2] = {W, W + d / WF::kKPerElem};
-    const size_t wstride = size_t(2) * d / WF::kKPerElem;
+    const uint8_t *W = reinterpret_cast<const uint8_t *>(slot + size_t(i0) * 2 * d / WF::kKPerElem);
+    const size_t row_bytes = size_t(d) / WF::kKPerElem * sizeof(typename WF::T);
+    const uint8_t *const wbase[2] = {W, W + row_bytes};
+    const size_t wstride = 2 * row_bytes;
     // MXFP4 block scales of W1 and W3 rows i0.. (unused by the other formats)
     const uint8_t *sc = reinterpret_cast<const uint8_t *>(slot) + size_t(3) * I * d / 2;
     const uint8_t *const sbase[2] = {sc + size_t(i0) * (d / 32),
                                      sc + size_t(I + i0) * (d / 32)};
-    const KBlocks kr = k_blocks(d, WF::template kb<MT>(), gridDim.z, blockIdx.z);
-    // The first block's weights load while the expert's pairs are looked up, with no
-    // branch in between (an empty split loads a clamped, valid block and drops it): at
-    // the join after a branch the compiler would wait for the weights before the scan.
-    WRegs<2, MT, WF> w;
-    w.load(wbase, wstride, sbase, size_t(d / 32), I - i0, d, kr.k0(0));
+    const KBlocks kr = k_blocks(d, S::KB, gridDim.z, blockIdx.z);
+    // The first block's weights load while the expert's pairs are looked up.  An empty
+    // split, or an expert without tokens, waits for them and drops them.
+    load_weights<2, S::kRowBytes, WF>(st0, wbase, wstride, I - i0, d, kr, 0);
     const int n_e = expert_pairs(ev, P, e, list, cnt);
-    if (n_e == 0) return;
-    for (int t0 = 0; t0 < n_e; t0 += 16 * MT) {
-        const void *xrow[MT];
-        bool xok[MT];
-#pragma unroll
-        for (int j = 0; j < MT; ++j) {
-            const int tok = t0 + (threadIdx.x >> 4) + 16 * j;
-            xok[j] = tok < n_e;
-            xrow[j] = x + size_t(list[xok[j] ? tok : 0] / k) * d;
-        }
-        floatx4 acc[2][MT];
-        gemm_tile<2, MT, ActF32, WF>(w, t0 == 0, wbase, wstride, sbase, size_t(d / 32), I - i0,
-                                     d, kr, xrow, xok, lds, acc);
+    const auto pass = [&](auto tiles, int t0) {
+        constexpr int NT = decltype(tiles)::value;
+        floatx4 acc[2][NT];
+        gemm_tile<2, MT, NT, ActF32, WF>(stage, xs, t0 == 0, wbase, wstride, sbase, size_t(d / 32),
+                                         I - i0, d, kr, list + t0, n_e - t0, k, x,
+                                         size_t(d) * sizeof(float), acc);
         const int i = i0 + 16 * wave + (lane & 15);
         float s1 = 1.f, s3 = 1.f;
         if constexpr (WF::kFp8) {
@@ -482,7 +533,7 @@ __global__ __launch_bounds__(kThreads) void up_gemm(
             s3 = i < I ? sc[I + i] : 0.f;
         }
 #pragma unroll
-        for (int tt = 0; tt < MT; ++tt)
+        for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int tok = t0 + 16 * tt + 4 * (lane >> 4) + r;
@@ -498,59 +549,55 @@ __global__ __launch_bounds__(kThreads) void up_gemm(
                 }
             }
         __syncthreads();   // LDS is reused by the next pass
+    };
+    for (int t0 = 0; t0 < n_e; t0 += 16 * MT) {
+        if (MT >= 2 && n_e - t0 <= 16) pass(Int<1>{}, t0);
+        else if (MT >= 4 && n_e - t0 <= 32) pass(Int<2>{}, t0);
+        else pass(Int<MT>{}, t0);
     }
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // no load into LDS outlives the workgroup
 }
 
 // down_gemm: grid (ceil(d / 64), E, SD).  64 rows j of W2 of expert blockIdx.y, K (= I)
 // blocks of split blockIdx.z.  yp[z * P*d + pair*d + j] = W2[j] . h[pair] over the split.
 // The activations are the bf16 h rows.
 template <int MT, class WF>
-__global__ __launch_bounds__(kThreads) void down_gemm(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void down_gemm(
     int d, int I, int P, const int32_t *__restrict__ exec_idx,
     const int32_t *__restrict__ slot_of_expert, int n_slots,
     const typename WF::T *__restrict__ slots, size_t slot_stride, const __bf16 *__restrict__ hb,
     float *__restrict__ yp) {
-    __shared__ __align__(16) GemmLds<1, MT, WF> lds;
-    __shared__ int list[APEX_MAX_PAIRS];
-    __shared__ int cnt[kPairRounds][4];
+    APEX_STAGES(1)
     const int e = blockIdx.y;
-    const int s = slot_of_expert[e];
-    if (s < 0 || s >= n_slots) return;
     int ev[kPairRounds];
     pair_ids(exec_idx, P, ev);
+    const int s = slot_of_expert[e];
+    if (s < 0 || s >= n_slots) return;
     const int j0 = blockIdx.x * kRows;
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const typename WF::T *slot = slots + size_t(s) * slot_stride;
-    const typename WF::T *const wbase[1] = {
-        slot + (size_t(2) * I * d + size_t(j0) * I) / WF::kKPerElem};
-    const size_t wstride = size_t(I) / WF::kKPerElem;
+    const uint8_t *const wbase[1] = {reinterpret_cast<const uint8_t *>(
+        slot + (size_t(2) * I * d + size_t(j0) * I) / WF::kKPerElem)};
+    const size_t wstride = size_t(I) / WF::kKPerElem * sizeof(typename WF::T);
     const uint8_t *const sbase[1] = {reinterpret_cast<const uint8_t *>(slot) +
                                      size_t(3) * I * d / 2 + size_t(2) * I * (d / 32) +
                                      size_t(j0) * (I / 32)};
-    const KBlocks kr = k_blocks(I, WF::template kb<MT>(), gridDim.z, blockIdx.z);
+    const KBlocks kr = k_blocks(I, S::KB, gridDim.z, blockIdx.z);
     // the first block's weights load while the expert's pairs are looked up (as in up_gemm)
-    WRegs<1, MT, WF> w;
-    w.load(wbase, wstride, sbase, size_t(I / 32), d - j0, I, kr.k0(0));
+    load_weights<1, S::kRowBytes, WF>(st0, wbase, wstride, d - j0, I, kr, 0);
     const int n_e = expert_pairs(ev, P, e, list, cnt);
-    if (n_e == 0) return;
     float *out = yp + size_t(blockIdx.z) * P * d;
-    for (int t0 = 0; t0 < n_e; t0 += 16 * MT) {
-        const void *hrow[MT];
-        bool hok[MT];
-#pragma unroll
-        for (int j = 0; j < MT; ++j) {
-            const int tok = t0 + (threadIdx.x >> 4) + 16 * j;
-            hok[j] = tok < n_e;
-            hrow[j] = hb + size_t(list[hok[j] ? tok : 0]) * I;
-        }
-        floatx4 acc[1][MT];
-        gemm_tile<1, MT, ActBf16, WF>(w, t0 == 0, wbase, wstride, sbase, size_t(I / 32), d - j0,
-                                      I, kr, hrow, hok, lds, acc);
+    const auto pass = [&](auto tiles, int t0) {
+        constexpr int NT = decltype(tiles)::value;
+        floatx4 acc[1][NT];
+        gemm_tile<1, MT, NT, ActBf16, WF>(stage, xs, t0 == 0, wbase, wstride, sbase,
+                                          size_t(I / 32), d - j0, I, kr, list + t0, n_e - t0, 1,
+                                          hb, size_t(I) * sizeof(__bf16), acc);
         const int j = j0 + 16 * wave + (lane & 15);
         float s2 = 1.f;
         if constexpr (WF::kFp8) s2 = j < d ? row_scales<WF>(slot, d, I)[2 * I + j] : 0.f;
 #pragma unroll
-        for (int tt = 0; tt < MT; ++tt)
+        for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int tok = t0 + 16 * tt + 4 * (lane >> 4) + r;
@@ -558,7 +605,13 @@ __global__ __launch_bounds__(kThreads) void down_gemm(
                     out[size_t(list[tok]) * d + j] = s2 * acc[0][tt][r];
             }
         __syncthreads();   // LDS is reused by the next pass
+    };
+    for (int t0 = 0; t0 < n_e; t0 += 16 * MT) {
+        if (MT >= 2 && n_e - t0 <= 16) pass(Int<1>{}, t0);
+        else if (MT >= 4 && n_e - t0 <= 32) pass(Int<2>{}, t0);
+        else pass(Int<MT>{}, t0);
     }
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // no load into LDS outlives the workgroup
 }
 
 // swiglu_reduce: h[pair, i] = bf16(silu(sum_z u_z) * sum_z v_z) from up_gemm's SU split
@@ -674,9 +727,9 @@ Plan plan_for(int B, int d, int I, int k, int E, int n_slots) {
     // token tiles per pass: enough for the whole batch on one expert up to 64 tokens
     pl.MT = B >= 48 ? 4 : (B >= 24 ? 2 : 1);
     const int experts = std::min(std::min(E, B * k), n_slots);
-    const int kb = pl.MT == 4   ? WF::template kb<4>()
-                   : pl.MT == 2 ? WF::template kb<2>()
-                                : WF::template kb<1>();
+    const int kb = pl.MT == 4   ? WF::template plan_kb<4>()
+                   : pl.MT == 2 ? WF::template plan_kb<2>()
+                                : WF::template plan_kb<1>();
     const int nb_d = (d + kb - 1) / kb, nb_i = (I + kb - 1) / kb;
     pl.SU = pick_splits((I + kRows - 1) / kRows * experts, nb_d, WF::kUpGroups, true, 3);
     pl.SD = pick_splits((d + kRows - 1) / kRows * experts, nb_i, 1024, false, 8);

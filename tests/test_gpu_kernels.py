@@ -366,6 +366,29 @@ def test_ffn_mfma_skewed_expert_takes_every_token(torch):
     print("skew", ffn_close(y, case.oracle(), "skewed"))
 
 
+# tokens per expert at the edges of the 16-token tiles (with none, one short, one full, one
+# over, and more than one pass), for each number of tiles per pass
+TILE_LOADS = {20: (16, 1, 3, 0), 44: (33, 10, 1, 0), 47: (17, 16, 14, 0), 120: (65, 33, 17, 5)}
+
+
+@pytest.mark.parametrize("B", list(TILE_LOADS))
+@pytest.mark.parametrize("weights,chunk", [("bf16", 8), ("fp8", 16), ("mxfp4", 32)])
+def test_ffn_mfma_tiles_and_blocks(torch, weights, chunk, B):
+    """Rows of 1 to 6 blocks of 128 bytes (the stages of the weight pipeline and one round
+    more), the last block of a single 16-byte chunk, for every count of token tiles."""
+    for n in range(1, 7):
+        d, I = chunk * (8 * (n - 1) + 1), chunk * (8 * (6 - n) + 1)
+        cfg = shape(f"tiles_{weights}_{B}_{n}", 560 + 10 * n + chunk, d, 4, 1, I=I)
+        # a case whose random lists use, and so make resident, all four experts
+        case = next(c for c in (FfnCase(torch, cfg, B, seed=s, weights=weights) for s in range(41, 99))
+                    if (c.table >= 0).all())
+        order = np.random.default_rng(n).permutation(np.repeat(np.arange(4), TILE_LOADS[B]))
+        case.exec_idx[:, 0] = order
+        y = case.run()
+        ffn_close(y, case.oracle(), f"{cfg.name}")
+        assert np.array_equal(y.view(np.uint32), case.run().view(np.uint32))
+
+
 def test_ffn_mfma_two_passes_equal_one(torch):
     cfg = shape("mfma_pass", 414, 392, 12, 4, I=200)
     case = FfnCase(torch, cfg, 24, seed=17, n_slots_extra=2)
