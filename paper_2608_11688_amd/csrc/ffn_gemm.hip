@@ -175,25 +175,37 @@ __device__ int expert_pairs(const int (&ev)[kPairRounds], int P, int e, uint16_t
     return base;
 }
 
-// The K blocks of split z of a K range cut into blocks of kb values: nb blocks from b_lo,
-// visited from a rotated start.  Workgroups start at different K blocks: tiles that run
-// side by side then read different offsets of their rows instead of all hitting the same
-// DRAM channels.
+// The K blocks of split z of a K range: units of plan_kb values (of which the split rule
+// shares out whole ones, and in whose order the sums are formed whatever the size of a
+// block), each of PER blocks of kb.  Units are visited from a rotated start: workgroups that
+// run side by side then read different offsets of their rows instead of all hitting the
+// same DRAM channels.  Blocks wholly past the end of K are left out.
+template <int PER>
 struct KBlocks {
-    int b_lo, nb, rot, kb;
+    int lo, units, rot, kb;
+    int nb;     // blocks of the split
+    int gap;    // the first block behind those left out (the last unit's)
+    int left;   // how many are left out
     __device__ __forceinline__ int k0(int b) const {
-        const int q = b + rot;
-        return (b_lo + (q >= nb ? q - nb : q)) * kb;
+        if (PER > 1 && b >= gap) b += left;
+        const int u = b / PER, q = u + rot;
+        return ((lo + (q >= units ? q - units : q)) * PER + b % PER) * kb;
     }
 };
 
-__device__ __forceinline__ KBlocks k_blocks(int K, int kb, int splits, int z) {
-    const int n = (K + kb - 1) / kb;
-    KBlocks r;
-    r.b_lo = z * n / splits;
-    r.nb = (z + 1) * n / splits - r.b_lo;
+template <int PER>
+__device__ __forceinline__ KBlocks<PER> k_blocks(int K, int kb, int splits, int z) {
+    const int n = (K + PER * kb - 1) / (PER * kb);
+    KBlocks<PER> r;
+    r.lo = z * n / splits;
+    const int hi = (z + 1) * n / splits;
+    r.units = hi - r.lo;
     r.kb = kb;
-    r.rot = int((blockIdx.x * 7u + blockIdx.y * 13u) % unsigned(r.nb > 0 ? r.nb : 1));
+    r.rot = int((blockIdx.x * 7u + blockIdx.y * 13u) % unsigned(r.units > 0 ? r.units : 1));
+    // the last unit of K is the split's last, visited units - 1 - rot units after the first
+    r.left = hi == n && r.units > 0 ? (n * PER * kb - K) / kb : 0;
+    r.gap = (r.units - r.rot) * PER - r.left;
+    r.nb = r.units * PER - r.left;
     return r;
 }
 
@@ -258,8 +270,10 @@ struct TileShape {
     // activation buffers: two take a barrier per block, one takes two
     static constexpr int XB = D == 3 || D * kStage + 2 * kXs + kList > 80 * 1024 ? 1 : 2;
     static constexpr int kLds = D * kStage + XB * kXs + kList;
+    static constexpr int PER = WF::template plan_kb<MT>() / KB;   // blocks per unit of KBlocks
     static constexpr int UN = D;   // blocks per unrolled round: a multiple of D and of PX
-    static_assert(kLds <= 80 * 1024 && UN % D == 0 && UN % PX == 0 && (XB == 1 || UN % 2 == 0), "tile");
+    static_assert(kLds <= 80 * 1024 && UN % D == 0 && UN % PX == 0 && (XB == 1 || UN % 2 == 0) &&
+                      WF::template plan_kb<MT>() % KB == 0, "tile");
 };
 
 template <int I>
@@ -284,20 +298,21 @@ constexpr int vmcnt_only(int n) {
 // last one loads nothing (offsets past the buffer's end).  Buffer loads: the compiler takes
 // global loads into LDS for accesses of either memory and waits for all of them at the
 // next use of any loaded register.
-template <int NW, int RB, class WF>
+template <int NW, int RB, class WF, class KR>
 __device__ __forceinline__ void load_weights(uint8_t *st, const uint8_t *const (&wbase)[NW],
                                              size_t wstride, int rows_valid, int K,
-                                             const KBlocks &kr, int b) {
+                                             const KR &kr, int b) {
     constexpr int CH = RB / 16, RPI = kWave / CH;   // chunks of a row, rows per instruction
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int k0 = kr.k0(min(b, kr.nb > 0 ? kr.nb - 1 : 0));
     const int row0 = min(16 * wave, rows_valid - 1);   // rows past the tile's last repeat it
+    const uint32_t bytes = b < kr.nb ? 0xffffffffu : 0u;
 #pragma unroll
     for (int m = 0; m < NW; ++m) {
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint8_t *>(wbase[m]) + size_t(row0) * wstride, 0,
-            b < kr.nb ? 0xffffffffu : 0u, 0x00027000);
+            bytes, 0x00027000);
 #pragma unroll
         for (int i = 0; i < 16 / RPI; ++i) {
             const int row = RPI * i + lane / CH;             // of the wavefront's 16
@@ -335,7 +350,8 @@ template <int NW, int MT, int NT, class Act, class WF, class Stage>
 __device__ __forceinline__ void gemm_tile(const Stage &stage, uint16_t *xs, bool w_ready,
                                           const uint8_t *const (&wbase)[NW], size_t wstride,
                                           const uint8_t *const (&sbase)[NW], size_t sstride,
-                                          int rows_valid, int K, const KBlocks &kr,
+                                          int rows_valid, int K,
+                                          const KBlocks<TileShape<NW, MT, WF>::PER> &kr,
                                           const uint16_t *list, int n_tok, int list_div,
                                           const void *act, size_t act_stride,
                                           floatx4 (&acc)[NW][NT]) {
@@ -514,7 +530,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     const uint8_t *sc = reinterpret_cast<const uint8_t *>(slot) + size_t(3) * I * d / 2;
     const uint8_t *const sbase[2] = {sc + size_t(i0) * (d / 32),
                                      sc + size_t(I + i0) * (d / 32)};
-    const KBlocks kr = k_blocks(d, S::KB, gridDim.z, blockIdx.z);
+    const auto kr = k_blocks<S::PER>(d, S::KB, gridDim.z, blockIdx.z);
     // The first block's weights load while the expert's pairs are looked up.  An empty
     // split, or an expert without tokens, waits for them and drops them.
     load_weights<2, S::kRowBytes, WF>(st0, wbase, wstride, I - i0, d, kr, 0);
@@ -582,7 +598,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     const uint8_t *const sbase[1] = {reinterpret_cast<const uint8_t *>(slot) +
                                      size_t(3) * I * d / 2 + size_t(2) * I * (d / 32) +
                                      size_t(j0) * (I / 32)};
-    const KBlocks kr = k_blocks(I, S::KB, gridDim.z, blockIdx.z);
+    const auto kr = k_blocks<S::PER>(I, S::KB, gridDim.z, blockIdx.z);
     // the first block's weights load while the expert's pairs are looked up (as in up_gemm)
     load_weights<1, S::kRowBytes, WF>(st0, wbase, wstride, d - j0, I, kr, 0);
     const int n_e = expert_pairs(ev, P, e, list, cnt);

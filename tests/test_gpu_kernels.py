@@ -374,10 +374,11 @@ TILE_LOADS = {20: (16, 1, 3, 0), 44: (33, 10, 1, 0), 47: (17, 16, 14, 0), 120: (
 @pytest.mark.parametrize("B", list(TILE_LOADS))
 @pytest.mark.parametrize("weights,chunk", [("bf16", 8), ("fp8", 16), ("mxfp4", 32)])
 def test_ffn_mfma_tiles_and_blocks(torch, weights, chunk, B):
-    """Rows of 1 to 6 blocks of 128 bytes (the stages of the weight pipeline and one round
-    more), the last block of a single 16-byte chunk, for every count of token tiles."""
-    for n in range(1, 7):
-        d, I = chunk * (8 * (n - 1) + 1), chunk * (8 * (6 - n) + 1)
+    """Rows of 1 to 12 lines of 128 bytes (one to six blocks of two lines: more than two rounds
+    of the weight stages), the last line of a single 16-byte chunk, for every count of token
+    tiles."""
+    for n, m in ((1, 6), (2, 5), (3, 4), (4, 3), (5, 2), (6, 1), (12, 9), (9, 12)):
+        d, I = chunk * (8 * (n - 1) + 1), chunk * (8 * (m - 1) + 1)
         cfg = shape(f"tiles_{weights}_{B}_{n}", 560 + 10 * n + chunk, d, 4, 1, I=I)
         # a case whose random lists use, and so make resident, all four experts
         case = next(c for c in (FfnCase(torch, cfg, B, seed=s, weights=weights) for s in range(41, 99))
@@ -387,6 +388,23 @@ def test_ffn_mfma_tiles_and_blocks(torch, weights, chunk, B):
         y = case.run()
         ffn_close(y, case.oracle(), f"{cfg.name}")
         assert np.array_equal(y.view(np.uint32), case.run().view(np.uint32))
+
+
+@pytest.mark.parametrize("d,I", [(1000, 776), (392, 1160)])
+def test_ffn_mfma_bf16_sums_do_not_depend_on_the_batch(torch, d, I):
+    """K is summed in one order whatever the number of token tiles (and with it the size of a
+    K block): with equal K splits a token's output has the same bits in every batch."""
+    cfg = shape(f"tiles_same_{d}", 590 + d % 7, d, 16, 4, I=I)
+    case = FfnCase(torch, cfg, 64, seed=29)
+    full, plans = case.run(), {}
+    all_x, all_idx, all_gate = case.x, case.exec_idx, case.gate
+    for B in (8, 16, 24, 40, 64):
+        case.B, case.x, case.exec_idx, case.gate = B, all_x[:B], all_idx[:B], all_gate[:B]
+        plan = native.apex_moe_ffn_plan(B, d, I, cfg.E, cfg.k, case.n_slots, "bf16")
+        plans.setdefault(plan[1:], set()).add(plan[0])
+        if plan[1:] == native.apex_moe_ffn_plan(64, d, I, cfg.E, cfg.k, case.n_slots, "bf16")[1:]:
+            assert np.array_equal(case.run().view(np.uint32), full[:B].view(np.uint32)), (B, plan)
+    assert {1, 2, 4} in plans.values(), plans
 
 
 def test_ffn_mfma_two_passes_equal_one(torch):
