@@ -109,10 +109,14 @@ __device__ void token_logits(const float *__restrict__ h, const uint16_t *__rest
     }
     __syncthreads();
     if (wave != 0) return;
-    float z = 0.f;
+    float z[WC];   // added pairwise: one after the other they rounded up to 15 times
 #pragma unroll
-    for (int q = 0; q < WC; ++q) z += part[q][lane];
-    if (lane < E) z_lds[lane] = z + (bias ? bias[lane] : 0.f);
+    for (int q = 0; q < WC; ++q) z[q] = part[q][lane];
+#pragma unroll
+    for (int n = WC / 2; n > 0; n /= 2)
+#pragma unroll
+        for (int q = 0; q < n; ++q) z[q] += z[q + n];
+    if (lane < E) z_lds[lane] = z[0] + (bias ? bias[lane] : 0.f);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");

@@ -136,6 +136,23 @@ def test_router_and_gate_shapes(torch, d, E, k):
     check_gate(torch, cfg, tokens(cfg, 33, which=1), native.MODE_STALL_FREE, avail, ledger=ledger)
 
 
+def test_router_logits_do_not_lose_small_partial_sums(torch):
+    """A logit of 2^24 plus one in each of 15 later pieces of d (a multiple of 128 values) is
+    2^24 + 15: pairwise sums give at least 2^24 + 14 (one addition of 1 to 2^24 is a tie),
+    one after the other each 1 is rounded away and expert 1 at 2^24 + 8 wins."""
+    d, E = 2048, 4
+    w = torch.zeros(E, d, dtype=torch.bfloat16, device="cuda")
+    w[0, ::128] = 1.0
+    w[0, 0] = w[1, 0] = 2.0 ** 24
+    w[1, 1] = 8.0
+    h = torch.ones(3, d, device="cuda")
+    i32 = dict(dtype=torch.int32, device="cuda")
+    idx, cnt = torch.full((3, 1), -1, **i32), torch.zeros(3, **i32)
+    native.apex_prefetch_route(h, w, None, 3, d, E, 1, 1, native.SEL_STATIC, 0.0, 0, None, None, idx,
+                               cnt, None)
+    assert (idx.cpu() == 0).all()
+
+
 def test_route_writes_pinned_host_memory(torch):
     cfg = configs.GRANITE_1B
     h = tokens(cfg, 8)
