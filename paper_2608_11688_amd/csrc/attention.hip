@@ -7,8 +7,10 @@
 //            to bf16 and stored at position pos of the caches.
 //   split    attn_split, grid (S, G, B): the tiles of 16 cached positions of one key/value
 //            head are shared out over S workgroups of four wavefronts for the H / G query
-//            heads that use the head; the workgroup that finishes a head last merges the S
-//            partial results (log-sum-exp rule) into the attention vector.
+//            heads that use the head.
+//   merge    attn_merge (S > 1), grid (H, B): the S partial results of a head merged
+//            (log-sum-exp rule) into the attention vector; up to kFewSplits splits of one
+//            token are merged by the output projection itself (gemv_merged).
 //   out      W_o a.
 // One token's projections are gemv (one wavefront per row), a batch's proj_mfma.
 // fp32 activations, scores, probabilities and sums on bf16 weights and caches; no float
@@ -50,9 +52,7 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 constexpr int kMaxGroup = 8;               // query heads per key/value head
 constexpr int kTile = 16;                  // cached positions per tile
-constexpr int kWsSplits = 256;             // position splits the workspace has room for
-constexpr int kMaxSplits = kWsSplits - 1;   // the last one's room holds the merge counters
-constexpr int kMaxSplitsBatch = 64;         // two or more tokens: pieces take the others' room
+constexpr int kMaxSplits = 256;            // position splits the workspace has room for
 
 __device__ __forceinline__ uint16_t bf16_bits(float v) {
     return __builtin_bit_cast(uint16_t, static_cast<__bf16>(v));
@@ -113,14 +113,12 @@ struct Dest {
 };
 
 // out[b, r] = W[r] . x[b], one wavefront per row, NPL 16-byte chunks of the row per lane in
-// flight together; grid (rows / 4, tokens).  `zero`: n_zero merge counters to clear.
+// flight together; grid (rows / 4, tokens).
 template <int NPL>
 __global__ __launch_bounds__(kThreads) void gemv(const float *__restrict__ x,
                                                  const uint16_t *__restrict__ w, int K, int R,
-                                                 Dest dst, int *__restrict__ zero, int n_zero) {
+                                                 Dest dst) {
     const int b = blockIdx.y;
-    const int first = (b * gridDim.x + blockIdx.x) * kThreads + threadIdx.x;
-    if (first < n_zero) zero[first] = 0;
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const int r = blockIdx.x * kWaves + wave;
     if (r >= R) return;
@@ -153,15 +151,11 @@ __device__ __forceinline__ size_t piece_at(int s, int tiles, int t, int q, int l
     return ((size_t(s) * tiles + t) * 3 + q) * kWave + l;
 }
 
-// Grid (steps * tiles / 4): the pieces of x, zeros past token B and past K.  Clears the
-// merge counters too.
+// Grid (steps * tiles / 4): the pieces of x, zeros past token B and past K.
 __global__ __launch_bounds__(kThreads) void split_x(const float *__restrict__ x, int B, int K,
                                                     int tiles, int n_pieces,
-                                                    uint4 *__restrict__ pieces,
-                                                    int *__restrict__ zero, int n_zero) {
-    const int first = blockIdx.x * kThreads + threadIdx.x;
-    for (int i = first; i < n_zero; i += gridDim.x * kThreads) zero[i] = 0;
-    const int st = first / kWave, lane = first % kWave;
+                                                    uint4 *__restrict__ pieces) {
+    const int st = blockIdx.x * kWaves + threadIdx.x / kWave, lane = threadIdx.x % kWave;
     if (st >= n_pieces) return;
     const int s = st / tiles, t = st - s * tiles;
     const int b = 16 * t + (lane & 15), k = 32 * s + 8 * (lane >> 4);
@@ -274,23 +268,6 @@ __global__ __launch_bounds__(kProjWaves *kWave)
     }
 }
 
-// Values passed between workgroups of one launch, which may run on dies with second-level
-// caches of their own: stored through those caches and loaded past them (relaxed agent
-// scope), with the stores complete before the flag that announces them.  Fences of agent
-// scope would write back and drop the whole cache, once per wavefront.
-template <class T>
-__device__ __forceinline__ void st_through(T *p, T v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <class T>
-__device__ __forceinline__ T ld_through(const T *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void stores_done() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // holds the compiler
-    __builtin_amdgcn_s_waitcnt(0x0f70);                      // vmcnt(0)
-}
-
 __device__ __forceinline__ float lane_value(float v, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
@@ -326,14 +303,14 @@ struct AttnOut {
 //           score lanes to the lanes of their position through LDS.
 // The wavefronts' states are merged in LDS (log-sum-exp rule).  With one split per head the
 // result goes to `out` directly; with more, every workgroup writes its weighted sums,
-// maximum and normaliser, and the one that adds the last count of its (token, head) merges
-// them in split order, unless `done` is NULL (gemv_merged does it).
+// maximum and normaliser, and attn_merge or gemv_merged merges the splits.
 template <int HD, int GR>
 __global__ __launch_bounds__(kThreads)
     __attribute__((amdgpu_waves_per_eu(HD == 128 && GR >= 4 ? 2 : 3))) void attn_split(
     const float *__restrict__ q, const uint16_t *__restrict__ k_cache,
-    const uint16_t *__restrict__ v_cache, int H, int G, int ctx_max, int n_pos, int per, int more, float scale,
-    float *part, float *part_m, float *part_l, int *done, AttnOut out) {
+    const uint16_t *__restrict__ v_cache, int H, int G, int ctx_max, int n_pos, int per, int more,
+    float scale, float *__restrict__ part, float *__restrict__ part_m, float *__restrict__ part_l,
+    AttnOut out) {
     constexpr int KS = HD / 32;              // matrix-core steps of a score
     constexpr int LPP = HD / 8;              // lanes per position of a value load
     constexpr int PPI = kWave / LPP;         // positions per value load
@@ -343,8 +320,6 @@ __global__ __launch_bounds__(kThreads)
     __shared__ __align__(16) float p_lds[kWaves][kTile][GP];
     __shared__ float red_m[kWaves][GR], red_l[kWaves][GR];
     __shared__ float red_acc[kWaves][GR][HD];
-    __shared__ float weight[GR][kWsSplits];
-    __shared__ int is_last;
     const int s = blockIdx.x, g = blockIdx.y, b = blockIdx.z, S = gridDim.x;
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const int n = lane & 15, lg = lane >> 4;
@@ -509,62 +484,56 @@ __global__ __launch_bounds__(kThreads)
             out.put(b, H * HD, (g * GR + i) * HD + dim, aa / ll);
         } else {
             const size_t at = (head0 + i) * S + s;
-            st_through(part + at * HD + dim, aa);
+            part[at * HD + dim] = aa;
             if (dim == 0) {
-                st_through(part_m + at, mm);
-                st_through(part_l + at, ll);
+                part_m[at] = mm;
+                part_l[at] = ll;
             }
         }
     }
-    if (S == 1 || !done) return;
-    // the last of this head's workgroups to get here merges them: the results of each are
-    // in memory before its count
-    stores_done();
+}
+
+// attn_merge: grid (H, B).  The S <= 256 splits of one query head merged by the log-sum-exp
+// rule: one split's weight per thread, then every thread sums its share of the splits' values
+// (S * hd / 256 of them, loaded eight at a time) and the shares meet in LDS.  A launch of its
+// own (about 1 us): merged by the split kernel's last workgroup of each head (a store, a count
+// and loads past the caches, one after the other) the call took, in us with the same
+// projections, Granite-1B one token at 4095 positions 20.4 instead of 14.2, 8 heads of one
+// group at 16383 68.5 instead of 20.8; Granite-3B 32 tokens at 1000 36.2 instead of 37.9.
+__global__ __launch_bounds__(kThreads) void attn_merge(const float *__restrict__ part,
+                                                       const float *__restrict__ part_m,
+                                                       const float *__restrict__ part_l, int S,
+                                                       int H, int hd, AttnOut out) {
+    __shared__ float w[kMaxSplits];
+    __shared__ float red[kWaves], sum[kWaves];
+    __shared__ float num[kThreads];
+    const int head = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
+    const int wave = t / kWave, lane = t % kWave;
+    const size_t at = (size_t(b) * H + head) * S;
+    const float m = t < S ? part_m[at + t] : -INFINITY, l = t < S ? part_l[at + t] : 0.f;
+    const float mw = row_max(m);
+    const float mx = fmaxf(fmaxf(lane_value(mw, 0), lane_value(mw, 16)),
+                           fmaxf(lane_value(mw, 32), lane_value(mw, 48)));
+    if (lane == 0) red[wave] = mx;
     __syncthreads();
-    if (threadIdx.x == 0)
-        is_last = __hip_atomic_fetch_add(done + size_t(b) * G + g, 1, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT) == S - 1;
+    const float M = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    const float wt = m == -INFINITY ? 0.f : expf(m - M);
+    w[t] = wt;
+    const float den = wave_sum(wt * l);
+    if (lane == 0) sum[wave] = den;
     __syncthreads();
-    if (!is_last) return;
-    for (int i = wave; i < GR; i += kWaves) {
-        const float *pm = part_m + (head0 + i) * S, *pl = part_l + (head0 + i) * S;
-        float mx[kWsSplits / kWave], lx[kWsSplits / kWave], M = -INFINITY, D = 0.f;
-#pragma unroll
-        for (int c = 0; c < kWsSplits / kWave; ++c) {
-            const int x = c * kWave + lane;
-            mx[c] = -INFINITY;
-            lx[c] = 0.f;
-            if (x < S) {
-                mx[c] = ld_through(pm + x);
-                lx[c] = ld_through(pl + x);
-            }
-            M = fmaxf(M, mx[c]);
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, kWave));
-#pragma unroll
-        for (int c = 0; c < kWsSplits / kWave; ++c) {
-            const float wx = mx[c] == -INFINITY ? 0.f : expf(mx[c] - M);
-            if (c * kWave + lane < S) weight[i][c * kWave + lane] = wx;
-            D = fmaf(wx, lx[c], D);
-        }
-        D = wave_sum(D);
-        if (lane == 0) red_l[0][i] = D;
-    }
+    const float D = sum[0] + sum[1] + sum[2] + sum[3];
+    const int dim = t % hd, s0 = t / hd, step = kThreads / hd;
+    const float *p = part + at * hd + dim;
+    float acc = 0.f;
+#pragma unroll 8
+    for (int s = s0; s < S; s += step) acc = fmaf(w[s], p[size_t(s) * hd], acc);
+    num[t] = acc;
     __syncthreads();
-    for (int idx = threadIdx.x; idx < GR * HD; idx += kThreads) {
-        const int i = idx / HD, dim = idx % HD;
-        const float *p = part + (head0 + i) * S * HD + dim;
-        float aa = 0.f;
-        for (int x0 = 0; x0 < S; x0 += 16) {
-            float v[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = ld_through(p + size_t(min(x0 + u, S - 1)) * HD);
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                if (x0 + u < S) aa = fmaf(weight[i][x0 + u], v[u], aa);
-        }
-        out.put(b, H * HD, (g * GR + i) * HD + dim, aa / red_l[0][i]);
+    if (t < hd) {
+        float v = 0.f;
+        for (int g = 0; g < step; ++g) v += num[g * hd + t];
+        out.put(b, H * hd, head * hd + t, v / D);
     }
 }
 
@@ -656,22 +625,21 @@ __global__ __launch_bounds__(kThreads) void gemv_merged(
 // 128, 2000 positions (262 MB of keys and values), us: 1 split 49, 2 46, 4 46, 8 52, 16 65
 // (5.7 TB/s at 2; with ordinary instead of non-temporal loads 52); one position per lane
 // group and step, unpipelined, with the scores reduced by shuffles: 1 split, 139.
-int pick_splits(int n_pos, int B, int G) {
+int pick_splits(int n_pos, int B, int G, int most) {
     const int want = (512 + B * G - 1) / (B * G);
     const int tiles = (n_pos + kTile - 1) / kTile;
-    return std::max(1, std::min({want, (tiles + kWaves - 1) / kWaves,
-                                 B == 1 ? kMaxSplits : kMaxSplitsBatch}));
+    return std::max(1, std::min({want, (tiles + kWaves - 1) / kWaves, most}));
 }
 
 void launch_gemv(hipStream_t st, const float *x, const uint16_t *w, int B, int K, int R,
-                 const Dest &dst, int *zero, int n_zero) {
+                 const Dest &dst) {
     const dim3 grid((R + kWaves - 1) / kWaves, B);
     const int nch = K / 8;
     const auto f = nch <= kWave       ? gemv<1>
                    : nch <= 2 * kWave ? gemv<2>
                    : nch <= 4 * kWave ? gemv<4>
                                       : gemv<8>;
-    hipLaunchKernelGGL(f, grid, dim3(kThreads), 0, st, x, w, K, R, dst, zero, n_zero);
+    hipLaunchKernelGGL(f, grid, dim3(kThreads), 0, st, x, w, K, R, dst);
 }
 
 template <int NT>
@@ -704,7 +672,7 @@ void launch_proj(hipStream_t st, const uint4 *pieces, const float *x, const uint
 template <int HD>
 void launch_split(int GR, dim3 grid, hipStream_t st, const float *q, const uint16_t *k_cache,
                   const uint16_t *v_cache, int H, int G, int ctx_max, int n_pos, float scale,
-                  float *part, float *part_m, float *part_l, int *done, const AttnOut &out) {
+                  float *part, float *part_m, float *part_l, const AttnOut &out) {
     const int tiles = (n_pos + kTile - 1) / kTile, workers = grid.x * kWaves;
     const auto f = GR == 1   ? attn_split<HD, 1>
                    : GR == 2 ? attn_split<HD, 2>
@@ -712,7 +680,7 @@ void launch_split(int GR, dim3 grid, hipStream_t st, const float *q, const uint1
                    : GR == 4 ? attn_split<HD, 4>
                              : attn_split<HD, 8>;
     hipLaunchKernelGGL(f, grid, dim3(kThreads), 0, st, q, k_cache, v_cache, H, G, ctx_max, n_pos,
-                       tiles / workers, tiles % workers, scale, part, part_m, part_l, done, out);
+                       tiles / workers, tiles % workers, scale, part, part_m, part_l, out);
 }
 
 }  // namespace
@@ -720,7 +688,7 @@ void launch_split(int GR, dim3 grid, hipStream_t st, const float *q, const uint1
 extern "C" size_t apex_attention_workspace_bytes(int B, int H, int G, int hd, int ctx_max) {
     if (B <= 0 || H <= 0 || G <= 0 || hd <= 0 || ctx_max <= 0) return 256;
     const size_t qb = apex::align_up(size_t(B) * H * hd * sizeof(float), 256);   // q, a
-    const size_t pb = size_t(B) * H * kWsSplits * (hd + 2) * sizeof(float);
+    const size_t pb = size_t(B) * H * kMaxSplits * (hd + 2) * sizeof(float);
     return 2 * qb + apex::align_up(pb, 256);
 }
 
@@ -760,53 +728,56 @@ extern "C" apex_status apex_attention_decode(const float *h, const uint16_t *w_q
     const int few_splits = std::min({(pos_tiles + kWaves - 1) / kWaves, kFewSplits,
                                      int(std::min(kFewBytes / split_bytes, size_t(kFewSplits)))});
     const bool few = B == 1 && few_splits > 0 && pos_tiles <= few_splits * kWaves * 4;
-    const int S = few ? few_splits : pick_splits(n_pos, B, G);
-    // workspace: q, a, then the room of kWsSplits splits (hd weighted sums, a maximum and a
-    // normaliser per head and token): the first ones' sums, maxima and normalisers, the
-    // pieces of a batch, and in the last one's room the merge counters
+    // workspace: q, a, then the room of kMaxSplits splits (hd weighted sums, a maximum and a
+    // normaliser per head and token).  A batch's pieces, 6 bytes a value and tokens up to whole
+    // tiles, take their place there: those of `h` before any split is written, those of `a`
+    // behind the splits
     const size_t qb = apex::align_up(size_t(B) * H * hd * sizeof(float), 256);
-    const size_t heads = size_t(B) * H;
-    const int max_splits = B == 1 ? kMaxSplits : kMaxSplitsBatch;
+    const size_t heads = size_t(B) * H, split_room = heads * (hd + 2) * sizeof(float);
+    const size_t room = kMaxSplits * split_room;
+    const int tiles = (B + 15) / 16;
+    const auto piece_bytes = [&](int K) {
+        return size_t((K + 31) / 32) * tiles * 3 * kWave * sizeof(uint4);
+    };
+    const size_t a_bytes = piece_bytes(H * hd);
     float *q = static_cast<float *>(workspace);
     float *a = reinterpret_cast<float *>(static_cast<char *>(workspace) + qb);
     float *part = reinterpret_cast<float *>(static_cast<char *>(workspace) + 2 * qb);
-    float *part_m = part + heads * max_splits * hd, *part_l = part_m + heads * max_splits;
-    int *done = reinterpret_cast<int *>(part + heads * kMaxSplits * (hd + 2));
-    const int n_done = S > 1 && !few ? B * G : 0;
-    // pieces: 6 bytes a value, tokens up to whole tiles.  Those of `a` always fit in the
-    // room of the splits between kMaxSplitsBatch and kMaxSplits (96 hd against 764 (hd + 2)
-    // bytes per head and token); those of h, d values wide, nearly always (d up to 8000 per
-    // query head), and go one token at a time where they do not
-    const int tiles = (B + 15) / 16, x_steps = (d + 31) / 32;
-    uint4 *pieces = reinterpret_cast<uint4 *>(
-        reinterpret_cast<char *>(part) +
-        apex::align_up(heads * kMaxSplitsBatch * (hd + 2) * sizeof(float), 256));
-    const size_t room = reinterpret_cast<char *>(done) - reinterpret_cast<char *>(pieces);
-    const size_t x_bytes = size_t(x_steps) * tiles * 3 * kWave * sizeof(uint4);
+    const bool mfma_out = B > 1;
+    const bool mfma_qkv = B > 1 && piece_bytes(d) <= room;
+    uint4 *x_pieces = reinterpret_cast<uint4 *>(part);
+    uint4 *a_pieces = reinterpret_cast<uint4 *>(reinterpret_cast<char *>(part) + (room - a_bytes) / 256 * 256);
+    const int most = mfma_out ? int((room - a_bytes - 256) / split_room) : kMaxSplits;
+    const int S = few ? few_splits : pick_splits(n_pos, B, G, most);
+    float *part_m = part + heads * S * hd, *part_l = part_m + heads * S;
 
     const int R = (H + 2 * G) * hd;
     const Dest qkv{q, k_cache, v_cache, G, hd, ctx_max, pos, H * hd};
-    if (B == 1 || x_bytes > room) {
-        launch_gemv(stream, h, w_qkv, B, d, R, qkv, done, n_done);
-    } else {
-        const int n = x_steps * tiles;
+    if (mfma_qkv) {
+        const int n = (d + 31) / 32 * tiles;
         hipLaunchKernelGGL(split_x, dim3((n + kWaves - 1) / kWaves), dim3(kThreads), 0, stream, h,
-                           B, d, tiles, n, pieces, done, n_done);
+                           B, d, tiles, n, x_pieces);
         APEX_HIP(hipGetLastError());
-        launch_proj(stream, pieces, h, w_qkv, B, d, R, qkv);
+        launch_proj(stream, x_pieces, h, w_qkv, B, d, R, qkv);
+    } else {
+        launch_gemv(stream, h, w_qkv, B, d, R, qkv);
     }
     APEX_HIP(hipGetLastError());
-    const AttnOut out{a, B == 1 ? nullptr : reinterpret_cast<uint16_t *>(pieces), tiles};
+    const AttnOut out{a, mfma_out ? reinterpret_cast<uint16_t *>(a_pieces) : nullptr, tiles};
     const float scale = 1.f / std::sqrt(float(hd));
     const dim3 grid(S, G, B);
-    int *counters = few ? nullptr : done;
     if (hd == 64)
         launch_split<64>(H / G, grid, stream, q, k_cache, v_cache, H, G, ctx_max, n_pos, scale,
-                         part, part_m, part_l, counters, out);
+                         part, part_m, part_l, out);
     else
         launch_split<128>(H / G, grid, stream, q, k_cache, v_cache, H, G, ctx_max, n_pos, scale,
-                          part, part_m, part_l, counters, out);
+                          part, part_m, part_l, out);
     APEX_HIP(hipGetLastError());
+    if (S > 1 && !few) {
+        hipLaunchKernelGGL(attn_merge, dim3(H, B), dim3(kThreads), 0, stream, part, part_m, part_l,
+                           S, H, hd, out);
+        APEX_HIP(hipGetLastError());
+    }
     const Dest dst{o, nullptr, nullptr, 1, 1, 1, 0, d};
     if (few && S > 1) {
         const int nch = H * hd / 8;
@@ -815,10 +786,10 @@ extern "C" apex_status apex_attention_decode(const float *h, const uint16_t *w_q
                                   : nch <= 4 * kWave ? gemv_merged<4> : gemv_merged<8>;
         hipLaunchKernelGGL(f, dim3((d + kWaves - 1) / kWaves), dim3(kThreads), lds, stream, part,
                            part_m, part_l, S, H, hd, w_o, d, o);
-    } else if (B == 1) {
-        launch_gemv(stream, a, w_o, B, H * hd, d, dst, nullptr, 0);
+    } else if (mfma_out) {
+        launch_proj(stream, a_pieces, a, w_o, B, H * hd, d, dst);
     } else {
-        launch_proj(stream, pieces, a, w_o, B, H * hd, d, dst);
+        launch_gemv(stream, a, w_o, B, H * hd, d, dst);
     }
     APEX_HIP(hipGetLastError());
     return APEX_OK;

@@ -129,8 +129,8 @@ def test_attention_infinite_operands_as_in_32_bit_arithmetic(torch, B):
 
 
 def test_attention_replayed_from_a_captured_graph(torch):
-    """The splits are merged by the workgroup that finishes last: its counters are cleared
-    by every call, so replays with other calls between them agree with the eager call."""
+    """Replays with other calls (of other sizes, in the same workspace) between them agree with
+    the eager call."""
     d, H, G, hd, pos, B = 256, 4, 2, 64, 700, 3
     g = torch.Generator(device="cuda").manual_seed(6)
     rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
