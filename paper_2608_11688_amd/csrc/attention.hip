@@ -658,6 +658,20 @@ void launch_proj_tiles(hipStream_t st, const uint4 *pieces, int tiles, const flo
                            dim3(kProjWaves * kWave), 0, st, pieces, tiles, x, w, B, K, R, dst);
 }
 
+// Whether the projection of two or more tokens (R rows of K values) goes to the matrix cores
+// (proj_mfma, `split`: with split_x before it) or one token at a time (gemv, which reads W for
+// each token, from the caches after the first at about 9.5 TB/s).  Fitted to ten shapes of 2
+// to 64 tokens with each projection on either path; where they cross, (B - 1) R is 15000 to
+// 38000 up to K = 1024, 10000 to 20000 at 1536 and 2048 and 9000 to 14000 at 4096.  Up to 32
+// row tiles the matrix-core kernel leaves most CUs idle and gemv was ahead at all of them.
+// A call of 8 tokens at pos 1000, us, matrix cores -> gemv: Granite-1B 23.6 -> 18.5, 8 heads
+// of one group at d = 1024 24.7 -> 18.3, OLMoE 36.5 -> 45.0, Mixtral 48.8 -> 96.5.
+bool use_mfma(int B, int K, int R, bool split) {
+    if (R <= 512 && B <= 64) return false;
+    const long long most = K <= 1024 ? 24000 : K <= 2048 ? 10000 : 8000;
+    return (B - 1LL) * R > most + (split ? 3000 : 0);
+}
+
 void launch_proj(hipStream_t st, const uint4 *pieces, const float *x, const uint16_t *w, int B,
                  int K, int R, const Dest &dst) {
     const int tiles = (B + 15) / 16;
@@ -743,8 +757,8 @@ extern "C" apex_status apex_attention_decode(const float *h, const uint16_t *w_q
     float *q = static_cast<float *>(workspace);
     float *a = reinterpret_cast<float *>(static_cast<char *>(workspace) + qb);
     float *part = reinterpret_cast<float *>(static_cast<char *>(workspace) + 2 * qb);
-    const bool mfma_out = B > 1;
-    const bool mfma_qkv = B > 1 && piece_bytes(d) <= room;
+    const bool mfma_out = B > 1 && use_mfma(B, H * hd, d, false);
+    const bool mfma_qkv = B > 1 && piece_bytes(d) <= room && use_mfma(B, d, (H + 2 * G) * hd, true);
     uint4 *x_pieces = reinterpret_cast<uint4 *>(part);
     uint4 *a_pieces = reinterpret_cast<uint4 *>(reinterpret_cast<char *>(part) + (room - a_bytes) / 256 * 256);
     const int most = mfma_out ? int((room - a_bytes - 256) / split_room) : kMaxSplits;
