@@ -625,9 +625,13 @@ __global__ __launch_bounds__(kThreads) void gemv_merged(
 // 128, 2000 positions (262 MB of keys and values), us: 1 split 49, 2 46, 4 46, 8 52, 16 65
 // (5.7 TB/s at 2; with ordinary instead of non-temporal loads 52); one position per lane
 // group and step, unpipelined, with the scores reduced by shuffles: 1 split, 139.
+// One split, without the merge, where the loop of a wavefront is then short against it: a
+// tile takes it less the fewer workgroups there are.  Call of 32 tokens, 24 heads of 64 in 8
+// groups, 200 positions 29.2 -> 26.3 us, 600 33.1 -> 32.3; 16 tokens at 200 24.3 -> 22.6.
 int pick_splits(int n_pos, int B, int G, int most) {
     const int want = (512 + B * G - 1) / (B * G);
     const int tiles = (n_pos + kTile - 1) / kTile;
+    if (25 * tiles <= kWaves * B * G) return 1;
     return std::max(1, std::min({want, (tiles + kWaves - 1) / kWaves, most}));
 }
 
