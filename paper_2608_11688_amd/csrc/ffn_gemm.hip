@@ -307,12 +307,15 @@ __device__ __forceinline__ void load_weights(uint8_t *st, const uint8_t *const (
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int k0 = kr.k0(min(b, kr.nb > 0 ? kr.nb - 1 : 0));
     const int row0 = min(16 * wave, rows_valid - 1);   // rows past the tile's last repeat it
-    const uint32_t bytes = b < kr.nb ? 0xffffffffu : 0u;
+    // In a scalar register by force: the select is made in a vector one, and a load whose
+    // descriptor is not known to be uniform is wrapped in a loop over the lanes' values
+    // (1172 of this file's 1822 direct loads, with the pipeline cut at each).
+    const int bytes = __builtin_amdgcn_readfirstlane(b < kr.nb ? -1 : 0);
 #pragma unroll
     for (int m = 0; m < NW; ++m) {
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint8_t *>(wbase[m]) + size_t(row0) * wstride, 0,
-            bytes, 0x00027000);
+            uint32_t(bytes), 0x00027000);
 #pragma unroll
         for (int i = 0; i < 16 / RPI; ++i) {
             const int row = RPI * i + lane / CH;             // of the wavefront's 16
