@@ -288,6 +288,11 @@ __device__ __forceinline__ int swizzle(int row) {
     return RB == 256 ? row & 15 : row >> 1;
 }
 
+// The register's value is taken here: the compiler waits for the load that fills it at this
+// point and moves no arithmetic on it to an earlier one (the zero test of a block scale went
+// to where the byte is requested, and the wait for it in front of the next weights' requests).
+__device__ __forceinline__ void settle(float &v) { asm volatile("" : "+v"(v)); }
+
 // The s_waitcnt operand that waits until at most n (capped) vector loads are outstanding.
 constexpr int vmcnt_only(int n) {
     n = n > 63 ? 63 : n;
@@ -418,9 +423,11 @@ __device__ __forceinline__ void gemm_tile(const Stage &stage, uint16_t *xs, bool
 #pragma unroll
         for (int m = 0; m < NW; ++m)
 #pragma unroll
-            for (int p = 0; p < P; ++p)
+            for (int p = 0; p < P; ++p) {
+                if constexpr (WF::kBlockScale) settle(sc[I % PX][m][p]);
                 scale[m][p] = WF::kBlockScale
                                   ? apex::ffn::mx_scale(__float_as_uint(sc[I % PX][m][p])) : 1.f;
+            }
         lds_barrier();
         load_x(b + PX, x, sc[I % PX]);
         load_weights<NW, S::kRowBytes, WF>(stage(Int<(I + D - 1) % D>{}), wbase, wstride, rows_valid, K, kr,
