@@ -289,9 +289,15 @@ __device__ __forceinline__ int swizzle(int row) {
 }
 
 // The register's value is taken here: the compiler waits for the load that fills it at this
-// point and moves no arithmetic on it to an earlier one (the zero test of a block scale went
-// to where the byte is requested, and the wait for it in front of the next weights' requests).
+// point and moves no arithmetic on it to an earlier one.
 __device__ __forceinline__ void settle(float &v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void settle(ActF32::Raw &r) {
+    asm volatile("" : "+v"(r.a.x), "+v"(r.a.y), "+v"(r.a.z), "+v"(r.a.w), "+v"(r.b.x), "+v"(r.b.y),
+                      "+v"(r.b.z), "+v"(r.b.w));
+}
+__device__ __forceinline__ void settle(ActBf16::Raw &r) {
+    asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w));
+}
 
 // The s_waitcnt operand that waits until at most n (capped) vector loads are outstanding.
 constexpr int vmcnt_only(int n) {
@@ -430,6 +436,7 @@ __device__ __forceinline__ void gemm_tile(const Stage &stage, uint16_t *xs, bool
             }
         lds_barrier();
         load_x(b + PX, x, sc[I % PX]);
+        __builtin_amdgcn_sched_barrier(0);
         load_weights<NW, S::kRowBytes, WF>(stage(Int<(I + D - 1) % D>{}), wbase, wstride, rows_valid, K, kr,
                              b + D - 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -462,6 +469,7 @@ __device__ __forceinline__ void gemm_tile(const Stage &stage, uint16_t *xs, bool
                 }
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
     // the requests ahead of the first block in the order of the later ones, so that the
     // compiler's count of loads at the top of the loop is the same on both ways into it
@@ -480,6 +488,19 @@ __device__ __forceinline__ void gemm_tile(const Stage &stage, uint16_t *xs, bool
     ahead(Int<0>{});
     ahead(Int<1>{});
     ahead(Int<2>{});
+    if constexpr (D == 2) {
+        // The first block's weights were requested before its activations where w_ready, after
+        // them in the loop.  Both are needed at once: waiting for them here leaves one order
+        // of requests at the top of the loop, where the compiler would otherwise wait for
+        // everything, the next block's weights among it.
+#pragma unroll
+        for (int j = 0; j < XP; ++j) settle(xraw[0][j]);
+        if constexpr (WF::kBlockScale)
+#pragma unroll
+            for (int m = 0; m < NW; ++m)
+#pragma unroll
+                for (int p = 0; p < P; ++p) settle(sc[0][m][p]);
+    }
     for (int b = 0; b < kr.nb; b += S::UN) {
         block(Int<0>{}, b);
         block(Int<1>{}, b + 1);
