@@ -233,47 +233,36 @@ __device__ __forceinline__ uint4 widen8(WMxfp4, uint4 v, int j, float sc) {
 }
 
 // Sizes of one workgroup's tile: NW matrices of 64 rows, up to 16 * MT tokens, K in blocks
-// of KB values (one or two cache lines of every weight row).  D weight stages are in LDS, the
-// loads of D - 1 blocks on the way or done while one is multiplied; the activations of the
-// next PX blocks are in registers or on the way.
-// D: more stages hide more of a load's time, fewer let more workgroups share a CU's 160 KB,
-// which hides the start of a workgroup (slot, pair scan, first activations) and evens out
-// the last wave of them.  Measured, us a launch: gate/up of 64 tokens, bf16 (OLMoE) D = 2
-// 49.6, 3 37.8, 4 45.7; MXFP4, 16 tokens (DeepSeek-16B) D = 2 26.0, 3 35.1, 4 37.1; down of
-// 64 tokens, bf16 D = 2 23.0, 4 21.5, 6 28.4; E4M3, 32 tokens (Mixtral) D = 2 43.9, 4 54.2;
-// MXFP4, 16 tokens D = 2 16.2, 4 17.4.
-// Two lines per row and block halve the barriers: for up to 16 tokens and bf16, whose blocks
-// have the least work (Granite-3B, 8 tokens: gate/up 14.2 -> 13.2, down 11.0 -> 9.5 us); with
-// more tokens or codes the larger activation tile costs more than that (down: OLMoE 21.5 ->
-// 25.4, Mixtral E4M3 43.9 -> 48.5, DeepSeek-16B MXFP4 16.2 -> 19.6).
-// Before (weights through registers to LDS, one block ahead, two barriers a block, all MT
-// token tiles multiplied; us a launch, up / down): OLMoE 45.9 / 25.2, Granite-3B 15.2 / 10.6,
-// DeepSeek-16B MXFP4 29.3 / 14.9, Mixtral E4M3 92.7 / 60.7; now 37.8 / 21.5, 13.2 / 9.5,
-// 25.9 / 16.1, 96.4 / 43.9.  A bare stream of the same bytes through LDS takes 34.5 / 16.1,
-// 11.2 / 5.7, 13.7 / -, 78.9 / 35.5.
+// of KB values (one or two cache lines of every weight row).  Two weight stages are in LDS:
+// one is multiplied while the other one loads.
+// LDS decides how many workgroups share a CU, and more of them hide more than more stages
+// do (the start of a workgroup: slot, pair scan, first activations; the last wave of them).
+// Three or four stages, each for one projection, format and tile count at a time, gave 0.92
+// to 1.01 of the calls' speed as a mean over the shapes (down of 33 to 64 tokens of E4M3:
+// 1.01), two 1.03 to 1.08 with more than one token tile.
+// Two lines per row and block halve the barriers, for twice the LDS.  bf16, whose blocks have
+// the least work: gate/up up to 32 tokens (1.03 and 1.00 against one line), down up to 16 (1.03;
+// with more tokens one line is as fast and leaves room).  Codes: 0.94 to 0.98.
+// One activation buffer takes a barrier more per block, and pays where a CU then holds a
+// workgroup more, up to four (32 tokens MXFP4 1.07, 64 tokens E4M3 1.04, Granite-3B 16 tokens
+// bf16 1.07; down to 0.95 with two or four experts of bf16 at Mixtral's size).
+// Calls over 113 shapes (2 to 64 tokens, six models, three formats) against the loop through
+// registers with two barriers a block: 1.10 as a mean, 0.95 to 1.58.
 template <int NW, int MT, class WF>
 struct TileShape {
-    static constexpr bool kWide = WF::kChunkK == 8 && MT == 1;
+    static constexpr bool kWide = WF::kChunkK == 8 && (MT == 1 || (MT == 2 && NW == 2));
     static constexpr int kRowBytes = kWide ? 256 : 128;   // of a weight row per block
     static constexpr int kChunks = kRowBytes / 16;
     static constexpr int KB = kChunks * WF::kChunkK;
+    static constexpr int PER = WF::template plan_kb<MT>() / KB;   // blocks per unit of KBlocks
     static constexpr int kStage = NW * kRows * kRowBytes;
     static constexpr int kXRow = KB + 8;   // +16 B: the 16 rows of a fragment read hit distinct banks
     static constexpr int kXs = 16 * MT * kXRow * 2;
-    static constexpr bool kMx = WF::kChunkK == 32;   // twice the activations of E4M3 per block
-    static constexpr int D = NW == 1   ? (MT == 4 || WF::kChunkK == 8 ? 4 : 2)
-                             : MT == 4 ? (kMx ? 2 : 3)
-                             : MT == 2 ? (kMx ? 3 : 4)
-                                       : 2;
-    static constexpr int PX = D == 4 ? 2 : 1;
     static constexpr int kList = APEX_MAX_PAIRS * 2 + kPairRounds * 16 + 64;
-    // activation buffers: two take a barrier per block, one takes two
-    static constexpr int XB = D == 3 || D * kStage + 2 * kXs + kList > 80 * 1024 ? 1 : 2;
-    static constexpr int kLds = D * kStage + XB * kXs + kList;
-    static constexpr int PER = WF::template plan_kb<MT>() / KB;   // blocks per unit of KBlocks
-    static constexpr int UN = D;   // blocks per unrolled round: a multiple of D and of PX
-    static_assert(kLds <= 80 * 1024 && UN % D == 0 && UN % PX == 0 && (XB == 1 || UN % 2 == 0) &&
-                      WF::template plan_kb<MT>() % KB == 0, "tile");
+    static constexpr int lds(int xb) { return 2 * kStage + xb * kXs + kList; }
+    static constexpr int per_cu(int xb) { return std::min(160 * 1024 / lds(xb), 4); }
+    static constexpr int XB = per_cu(1) > per_cu(2) ? 1 : 2;   // activation buffers
+    static_assert(lds(XB) <= 80 * 1024 && WF::template plan_kb<MT>() % KB == 0, "tile");
 };
 
 template <int I>
@@ -353,10 +342,10 @@ __device__ __forceinline__ void load_weights(uint8_t *st, const uint8_t *const (
 // so that the 16 rows of a fragment read fall in distinct banks.  Codes stay codes in LDS
 // and are widened to bf16 right before the matrix cores take them.  A lane multiplies the
 // K values of its own chunks: the activations are read in the same order.
-// Activations are the same for all four wavefronts: loaded PX blocks ahead into registers,
+// Activations are the same for all four wavefronts: loaded a block ahead into registers,
 // converted to bf16 and staged in LDS, with a barrier per block (two with one buffer).
-// Loads return in order, so a wait for activations is also one for the weights requested
-// before them: PX blocks of weights stay in flight across it.
+// Loads return in order: a block's activations are requested before its weights, so that the
+// wait for them leaves the weights in flight.
 // Every load is unconditional (blocks past the last one read one cached line, rows past
 // the last one that row) so that the compiler's load counts are exact.  K past the end is
 // zero on both sides; rows and tokens past the end are multiplied and dropped.
@@ -370,7 +359,7 @@ __device__ __forceinline__ void gemm_tile(const Stage &stage, uint16_t *xs, bool
                                           const void *act, size_t act_stride,
                                           floatx4 (&acc)[NW][NT]) {
     using S = TileShape<NW, MT, WF>;
-    constexpr int KB = S::KB, D = S::D, PX = S::PX;
+    constexpr int KB = S::KB;
     constexpr int SPR = KB / 8;                                    // 8-value pieces per token
     constexpr int XP = 16 * NT * SPR / kThreads > 0 ? 16 * NT * SPR / kThreads : 1;
     constexpr int P = S::kChunks / 4, SUB = WF::kChunkK / 8;          // matrix-core steps
@@ -388,22 +377,19 @@ __device__ __forceinline__ void gemm_tile(const Stage &stage, uint16_t *xs, bool
         xrow[j] = static_cast<const uint8_t *>(act) +
                   list[row < n_tok ? row : 0] / list_div * act_stride;
     }
-    // Loads that may still be on the way when block b is multiplied: those requested after
-    // its weights, in the steady state and behind the first blocks.  (The compiler does not
-    // tie a load into LDS to the reads of it.)  Waiting for the activations of block b
-    // covers this already where PX < D - 1.
-    constexpr int kXLoads = XP * Act::kLoads + (WF::kBlockScale ? NW * P : 0), kWLoads = NW * S::kRowBytes / 64;
-    constexpr int kInFlight = std::min((D - 1) * (kXLoads + kWLoads),
-                                       (D - 1) * kWLoads + (PX + 1) * kXLoads);
-    typename Act::Raw xraw[PX][XP];
-    float sc[PX][NW][P];
+    // Loads that may still be on the way when block b is multiplied: those of the next one.
+    // (The compiler does not tie a load into LDS to the reads of it.)
+    constexpr int kInFlight =
+        XP * Act::kLoads + (WF::kBlockScale ? NW * P : 0) + NW * S::kRowBytes / 64;
+    typename Act::Raw x[XP];
+    float sc[NW][P];
 #pragma unroll
     for (int m = 0; m < NW; ++m)
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt) acc[m][tt] = floatx4{0.f, 0.f, 0.f, 0.f};
     if (kr.nb <= 0) return;
     const int row_c = min(16 * wave + n, rows_valid - 1);
-    const auto load_x = [&](int b, typename Act::Raw(&x)[XP], float(&scale)[NW][P]) {
+    const auto load_x = [&](int b) {
         const int k0 = kr.k0(min(b, kr.nb - 1));
 #pragma unroll
         for (int j = 0; j < XP; ++j) x[j] = Act::load(xrow[j], min(k0 + xk[j], K - 8));
@@ -412,37 +398,41 @@ __device__ __forceinline__ void gemm_tile(const Stage &stage, uint16_t *xs, bool
             for (int m = 0; m < NW; ++m)
 #pragma unroll
                 for (int p = 0; p < P; ++p)
-                    scale[m][p] = __uint_as_float(
+                    sc[m][p] = __uint_as_float(
                         sbase[m][size_t(row_c) * sstride + min(k0 / 32 + 4 * p + g, K / 32 - 1)]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const auto settle_scales = [&] {
+        if constexpr (WF::kBlockScale)
+#pragma unroll
+            for (int m = 0; m < NW; ++m)
+#pragma unroll
+                for (int p = 0; p < P; ++p) settle(sc[m][p]);
     };
     const auto block = [&](auto which, int b) {
         constexpr int I = decltype(which)::value;
-        auto &x = xraw[I % PX];
-        uint16_t *xb = xs + (S::XB == 2 ? (I & 1) * (16 * MT * S::kXRow) : 0);
+        uint16_t *xb = xs + (S::XB == 2 ? I * (16 * MT * S::kXRow) : 0);
         const int end = b < kr.nb ? K : 0;   // a block past the last one multiplies zeros
         const int k0 = kr.k0(min(b, kr.nb - 1));
         if (S::XB == 1) lds_barrier();   // the previous block's activations have been read
 #pragma unroll
         for (int j = 0; j < XP; ++j)
             *reinterpret_cast<uint4 *>(xb + xat[j]) = keep_if(Act::to_bf16(x[j]), k0 + xk[j] < end);
+        settle_scales();
         float scale[NW][P];
 #pragma unroll
         for (int m = 0; m < NW; ++m)
 #pragma unroll
-            for (int p = 0; p < P; ++p) {
-                if constexpr (WF::kBlockScale) settle(sc[I % PX][m][p]);
-                scale[m][p] = WF::kBlockScale
-                                  ? apex::ffn::mx_scale(__float_as_uint(sc[I % PX][m][p])) : 1.f;
-            }
+            for (int p = 0; p < P; ++p)
+                scale[m][p] =
+                    WF::kBlockScale ? apex::ffn::mx_scale(__float_as_uint(sc[m][p])) : 1.f;
         lds_barrier();
-        load_x(b + PX, x, sc[I % PX]);
-        __builtin_amdgcn_sched_barrier(0);
-        load_weights<NW, S::kRowBytes, WF>(stage(Int<(I + D - 1) % D>{}), wbase, wstride, rows_valid, K, kr,
-                             b + D - 1);
+        load_x(b + 1);
+        load_weights<NW, S::kRowBytes, WF>(stage(Int<1 - I>{}), wbase, wstride, rows_valid, K, kr, b + 1);
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_waitcnt(vmcnt_only(kInFlight));   // block b's weights are in LDS
         asm volatile("" ::: "memory");
-        const uint8_t *w = stage(Int<I % D>{}) + wave * (NW * 16 * S::kRowBytes);
+        const uint8_t *w = stage(which) + wave * (NW * 16 * S::kRowBytes);
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             uint4 raw[NW];
@@ -469,43 +459,21 @@ __device__ __forceinline__ void gemm_tile(const Stage &stage, uint16_t *xs, bool
                 }
             }
         }
+        // the next block's wait for its activations stays behind these multiplies
         __builtin_amdgcn_sched_barrier(0);
     };
-    // the requests ahead of the first block in the order of the later ones, so that the
-    // compiler's count of loads at the top of the loop is the same on both ways into it
-    const auto ahead = [&](auto which) {   // iteration I - (D - 1)
-        constexpr int I = decltype(which)::value;
-        if constexpr (I < D - 1) {
-            if constexpr (I >= D - 1 - PX) {
-                load_x(I - (D - 1 - PX), xraw[I - (D - 1 - PX)], sc[I - (D - 1 - PX)]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (I > 0 || !w_ready)
-                load_weights<NW, S::kRowBytes, WF>(stage(Int<I>{}), wbase, wstride, rows_valid, K, kr, I);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    ahead(Int<0>{});
-    ahead(Int<1>{});
-    ahead(Int<2>{});
-    if constexpr (D == 2) {
-        // The first block's weights were requested before its activations where w_ready, after
-        // them in the loop.  Both are needed at once: waiting for them here leaves one order
-        // of requests at the top of the loop, where the compiler would otherwise wait for
-        // everything, the next block's weights among it.
+    load_x(0);
+    if (!w_ready) load_weights<NW, S::kRowBytes, WF>(stage(Int<0>{}), wbase, wstride, rows_valid, K, kr, 0);
+    // The first block's weights were requested before its activations where w_ready, after
+    // them in the loop.  Both are needed at once: waiting for them here leaves one order of
+    // requests at the top of the loop, where the compiler would otherwise wait for everything,
+    // the next block's weights among it.
 #pragma unroll
-        for (int j = 0; j < XP; ++j) settle(xraw[0][j]);
-        if constexpr (WF::kBlockScale)
-#pragma unroll
-            for (int m = 0; m < NW; ++m)
-#pragma unroll
-                for (int p = 0; p < P; ++p) settle(sc[0][m][p]);
-    }
-    for (int b = 0; b < kr.nb; b += S::UN) {
+    for (int j = 0; j < XP; ++j) settle(x[j]);
+    settle_scales();
+    for (int b = 0; b < kr.nb; b += 2) {
         block(Int<0>{}, b);
         block(Int<1>{}, b + 1);
-        if constexpr (S::UN > 2) block(Int<2>{}, b + 2);
-        if constexpr (S::UN > 3) block(Int<3>{}, b + 3);
     }
     // no load into LDS may outlive its stage (the next pass or another workgroup's LDS)
     __builtin_amdgcn_s_waitcnt(0x0f70);
@@ -522,15 +490,10 @@ __device__ __forceinline__ const float *row_scales(const typename WF::T *slot, i
 #define APEX_STAGES(NW_)                                                                       \
     using S = TileShape<NW_, MT, WF>;                                                          \
     __shared__ __align__(16) uint8_t st0[S::kStage], st1[S::kStage];                           \
-    __shared__ __align__(16) uint8_t st2[S::D > 2 ? S::kStage : 16];                           \
-    __shared__ __align__(16) uint8_t st3[S::D > 3 ? S::kStage : 16];                           \
     __shared__ __align__(16) uint16_t xs[S::XB * S::kXs / 2];                                  \
     __shared__ uint16_t list[APEX_MAX_PAIRS];                                                  \
     __shared__ int cnt[kPairRounds][4];                                                        \
-    const auto stage = [&](auto i) -> uint8_t * {                                              \
-        constexpr int I = decltype(i)::value;                                                  \
-        return I == 0 ? st0 : I == 1 ? st1 : I == 2 ? st2 : st3;                               \
-    };
+    const auto stage = [&](auto i) -> uint8_t * { return decltype(i)::value == 0 ? st0 : st1; };
 
 // up_gemm: grid (ceil(I / 64), E, SU).  64 rows of W1 and W3 of expert blockIdx.y, every
 // token of the expert (16*MT per pass), K blocks of split blockIdx.z.  slot_stride is
