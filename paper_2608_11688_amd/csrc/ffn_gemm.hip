@@ -24,6 +24,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 
 #include "ffn_device.h"
 #include "ffn_internal.h"
@@ -236,18 +237,18 @@ __device__ __forceinline__ uint4 widen8(WMxfp4, uint4 v, int j, float sc) {
 // of KB values (one or two cache lines of every weight row).  Two weight stages are in LDS:
 // one is multiplied while the other one loads.
 // LDS decides how many workgroups share a CU, and more of them hide more than more stages
-// do (the start of a workgroup: slot, pair scan, first activations; the last wave of them).
-// Three or four stages, each for one projection, format and tile count at a time, gave 0.92
-// to 1.01 of the calls' speed as a mean over the shapes (down of 33 to 64 tokens of E4M3:
-// 1.01), two 1.03 to 1.08 with more than one token tile.
-// Two lines per row and block halve the barriers, for twice the LDS.  bf16, whose blocks have
-// the least work: gate/up up to 32 tokens (1.03 and 1.00 against one line), down up to 16 (1.03;
-// with more tokens one line is as fast and leaves room).  Codes: 0.94 to 0.98.
+// do (the start of a workgroup: slot, pair scan, first activations; the last round of them).
+// With three or four stages, for one projection, format and tile count at a time, calls ran
+// at 0.93 to 1.01 of the speed with two.
+// Two lines per row and block halve the barriers, for twice the LDS: bf16, whose blocks have
+// the least work, gate/up up to 32 tokens (1.03 against one line) and down up to 16 (1.02;
+// with more tokens 0.99 to 1.01).  Codes: 0.94 to 1.00.
 // One activation buffer takes a barrier more per block, and pays where a CU then holds a
-// workgroup more, up to four (32 tokens MXFP4 1.07, 64 tokens E4M3 1.04, Granite-3B 16 tokens
-// bf16 1.07; down to 0.95 with two or four experts of bf16 at Mixtral's size).
-// Calls over 113 shapes (2 to 64 tokens, six models, three formats) against the loop through
-// registers with two barriers a block: 1.10 as a mean, 0.95 to 1.58.
+// workgroup more, up to four (32 tokens MXFP4 1.06 as a mean, 64 tokens E4M3 1.04, Granite-3B
+// 16 tokens bf16 1.07).
+// Calls of 221 shapes (2 to 64 tokens, six models with all or some experts resident, three
+// formats) against the loop through registers with two barriers a block: 1.11 as a mean,
+// 0.94 to 1.58.
 template <int NW, int MT, class WF>
 struct TileShape {
     static constexpr bool kWide = WF::kChunkK == 8 && (MT == 1 || (MT == 2 && NW == 2));
@@ -751,33 +752,57 @@ Plan plan_for(int B, int d, int I, int k, int E, int n_slots) {
     return pl;
 }
 
+// LDS to ask for beyond a tile's own, so that a CU takes at most an even share of the launch:
+// the hardware fills a CU before it looks at the next one, and while it does, the workgroups of
+// experts without a slot come and go, so that some CUs end up with three or four workgroups
+// and others with none.  The number per CU (two at least) is the one with which the rounds of
+// workgroups (of up to 1024; more level out by themselves) take least, a round's time going
+// by how many share the CU.  Counted are the experts that have a slot: those without tokens
+// load a block and leave, and would hold up the others.
+// us a call, without -> with: OLMoE, 24 experts of 64 resident, 64 tokens bf16 77.8 -> 65.4 (three
+// stages, so two workgroups a CU: 68.2), all resident 142.8 -> 130.0; Mixtral 4 of 8, 32 tokens
+// E4M3 143.5 -> 132.8; OLMoE 24, 8 tokens MXFP4 43.6 -> 35.6.  Over 221 shapes 1.02 as a mean,
+// 0.93 to 1.25.
+template <int NW, int MT, class WF>
+size_t lds_pad(dim3 g, int experts) {
+    using S = TileShape<NW, MT, WF>;
+    const int n = int(g.x * g.z) * experts, most = std::min(160 * 1024 / S::lds(S::XB), 8);
+    if (n > 1024) return 0;
+    int per = most, best = INT_MAX;
+    for (int c = most; c >= 2; --c) {
+        const int time = (n + 256 * c - 1) / (256 * c) * c;
+        if (time < best) best = time, per = c;
+    }
+    return per == most ? 0 : std::max(0, 160 * 1024 / (per + 1) + 1024 - S::lds(S::XB));
+}
+
 template <int MT, int SU, class WF>
-void launch_up(dim3 g, hipStream_t st, const float *x, int d, int I, int P, int k,
+void launch_up(dim3 g, int experts, hipStream_t st, const float *x, int d, int I, int P, int k,
                const int32_t *exec_idx, const int32_t *soe, int n_slots,
                const typename WF::T *slots, size_t stride, __bf16 *hb, float *uv) {
-    hipLaunchKernelGGL((up_gemm<MT, SU, WF>), g, dim3(kThreads), 0, st, x, d, I, P, k, exec_idx,
+    hipLaunchKernelGGL((up_gemm<MT, SU, WF>), g, dim3(kThreads), (lds_pad<2, MT, WF>(g, experts)), st, x, d, I, P, k, exec_idx,
                        soe, n_slots, slots, stride, hb, uv);
 }
 
 template <int MT, class WF>
-void launch_up_splits(int SU, dim3 g, hipStream_t st, const float *x, int d, int I, int P, int k,
+void launch_up_splits(int SU, dim3 g, int experts, hipStream_t st, const float *x, int d, int I, int P, int k,
                       const int32_t *exec_idx, const int32_t *soe, int n_slots,
                       const typename WF::T *slots, size_t stride, __bf16 *hb, float *uv) {
     if (SU == 1)
-        launch_up<MT, 1, WF>(g, st, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
+        launch_up<MT, 1, WF>(g, experts, st, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
     else if (SU == 2)
-        launch_up<MT, 2, WF>(g, st, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
+        launch_up<MT, 2, WF>(g, experts, st, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
     else if (SU == 3)
-        launch_up<MT, 3, WF>(g, st, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
+        launch_up<MT, 3, WF>(g, experts, st, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
     else
-        launch_up<MT, 4, WF>(g, st, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
+        launch_up<MT, 4, WF>(g, experts, st, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
 }
 
 template <int MT, class WF>
-void launch_down(dim3 g, hipStream_t st, int d, int I, int P, const int32_t *exec_idx,
+void launch_down(dim3 g, int experts, hipStream_t st, int d, int I, int P, const int32_t *exec_idx,
                  const int32_t *soe, int n_slots, const typename WF::T *slots, size_t stride,
                  const __bf16 *hb, float *yp) {
-    hipLaunchKernelGGL((down_gemm<MT, WF>), g, dim3(kThreads), 0, st, d, I, P, exec_idx, soe,
+    hipLaunchKernelGGL((down_gemm<MT, WF>), g, dim3(kThreads), (lds_pad<1, MT, WF>(g, experts)), st, d, I, P, exec_idx, soe,
                        n_slots, slots, stride, hb, yp);
 }
 
@@ -789,18 +814,19 @@ apex_status run_grouped(const float *x, int B, int d, int I, int E, int k,
                         int n_slots, float *y, int accumulate, char *wsb, hipStream_t stream) {
     const Plan pl = plan_for<WF>(B, d, I, k, E, n_slots);
     const int P = B * k;
+    const int experts = std::min(E, n_slots);
     float *uv = reinterpret_cast<float *>(wsb);
     __bf16 *hb = reinterpret_cast<__bf16 *>(wsb + pl.uv_bytes);
     float *yp = reinterpret_cast<float *>(wsb + apex::align_up(pl.h_bytes, 256));
     const dim3 gu((I + kRows - 1) / kRows, E, pl.SU);
     if (pl.MT == 4)
-        launch_up_splits<4, WF>(pl.SU, gu, stream, x, d, I, P, k, exec_idx, soe, n_slots, slots,
+        launch_up_splits<4, WF>(pl.SU, gu, experts, stream, x, d, I, P, k, exec_idx, soe, n_slots, slots,
                                 stride, hb, uv);
     else if (pl.MT == 2)
-        launch_up_splits<2, WF>(pl.SU, gu, stream, x, d, I, P, k, exec_idx, soe, n_slots, slots,
+        launch_up_splits<2, WF>(pl.SU, gu, experts, stream, x, d, I, P, k, exec_idx, soe, n_slots, slots,
                                 stride, hb, uv);
     else
-        launch_up_splits<1, WF>(pl.SU, gu, stream, x, d, I, P, k, exec_idx, soe, n_slots, slots,
+        launch_up_splits<1, WF>(pl.SU, gu, experts, stream, x, d, I, P, k, exec_idx, soe, n_slots, slots,
                                 stride, hb, uv);
     APEX_HIP(hipGetLastError());
     if (pl.SU > 1) {
@@ -819,11 +845,11 @@ apex_status run_grouped(const float *x, int B, int d, int I, int E, int k,
 
     const dim3 gd((d + kRows - 1) / kRows, E, pl.SD);
     if (pl.MT == 4)
-        launch_down<4, WF>(gd, stream, d, I, P, exec_idx, soe, n_slots, slots, stride, hb, yp);
+        launch_down<4, WF>(gd, experts, stream, d, I, P, exec_idx, soe, n_slots, slots, stride, hb, yp);
     else if (pl.MT == 2)
-        launch_down<2, WF>(gd, stream, d, I, P, exec_idx, soe, n_slots, slots, stride, hb, yp);
+        launch_down<2, WF>(gd, experts, stream, d, I, P, exec_idx, soe, n_slots, slots, stride, hb, yp);
     else
-        launch_down<1, WF>(gd, stream, d, I, P, exec_idx, soe, n_slots, slots, stride, hb, yp);
+        launch_down<1, WF>(gd, experts, stream, d, I, P, exec_idx, soe, n_slots, slots, stride, hb, yp);
     APEX_HIP(hipGetLastError());
     const dim3 gc((d / 4 + kThreads - 1) / kThreads, B);
     if (pl.SD == 1)
