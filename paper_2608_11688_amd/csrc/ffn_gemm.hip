@@ -240,19 +240,17 @@ __device__ __forceinline__ uint4 widen8(WMxfp4, uint4 v, int j, float sc) {
 // do (the start of a workgroup: slot, pair scan, first activations; the last round of them).
 // With three or four stages, for one projection, format and tile count at a time, calls ran
 // at 0.93 to 1.01 of the speed with two.
-// Two lines per row and block halve the barriers, for twice the LDS: bf16, whose blocks have
-// the least work, gate/up up to 32 tokens (1.03 against one line) and down up to 16 (1.02;
-// with more tokens 0.99 to 1.01).  Codes: 0.94 to 1.00.
+// Two lines per row and block (W; a block is then the plan's unit) halve the barriers, for
+// twice the LDS: see wide_rows.
 // One activation buffer takes a barrier more per block, and pays where a CU then holds a
 // workgroup more, up to four (32 tokens MXFP4 1.06 as a mean, 64 tokens E4M3 1.04, Granite-3B
 // 16 tokens bf16 1.07).
 // Calls of 221 shapes (2 to 64 tokens, six models with all or some experts resident, three
 // formats) against the loop through registers with two barriers a block: 1.11 as a mean,
 // 0.94 to 1.58.
-template <int NW, int MT, class WF>
+template <int NW, int MT, class WF, bool W>
 struct TileShape {
-    static constexpr bool kWide = WF::kChunkK == 8 && (MT == 1 || (MT == 2 && NW == 2));
-    static constexpr int kRowBytes = kWide ? 256 : 128;   // of a weight row per block
+    static constexpr int kRowBytes = W ? 256 : 128;   // of a weight row per block
     static constexpr int kChunks = kRowBytes / 16;
     static constexpr int KB = kChunks * WF::kChunkK;
     static constexpr int PER = WF::template plan_kb<MT>() / KB;   // blocks per unit of KBlocks
@@ -350,16 +348,16 @@ __device__ __forceinline__ void load_weights(uint8_t *st, const uint8_t *const (
 // Every load is unconditional (blocks past the last one read one cached line, rows past
 // the last one that row) so that the compiler's load counts are exact.  K past the end is
 // zero on both sides; rows and tokens past the end are multiplied and dropped.
-template <int NW, int MT, int NT, class Act, class WF, class Stage>
+template <int NW, int MT, int NT, bool W, class Act, class WF, class Stage>
 __device__ __forceinline__ void gemm_tile(const Stage &stage, uint16_t *xs, bool w_ready,
                                           const uint8_t *const (&wbase)[NW], size_t wstride,
                                           const uint8_t *const (&sbase)[NW], size_t sstride,
                                           int rows_valid, int K,
-                                          const KBlocks<TileShape<NW, MT, WF>::PER> &kr,
+                                          const KBlocks<TileShape<NW, MT, WF, W>::PER> &kr,
                                           const uint16_t *list, int n_tok, int list_div,
                                           const void *act, size_t act_stride,
                                           floatx4 (&acc)[NW][NT]) {
-    using S = TileShape<NW, MT, WF>;
+    using S = TileShape<NW, MT, WF, W>;
     constexpr int KB = S::KB;
     constexpr int SPR = KB / 8;                                    // 8-value pieces per token
     constexpr int XP = 16 * NT * SPR / kThreads > 0 ? 16 * NT * SPR / kThreads : 1;
@@ -489,7 +487,7 @@ __device__ __forceinline__ const float *row_scales(const typename WF::T *slot, i
 // The stages of a tile: LDS arrays of their own, so that the compiler tells a load into one
 // from a read of another.
 #define APEX_STAGES(NW_)                                                                       \
-    using S = TileShape<NW_, MT, WF>;                                                          \
+    using S = TileShape<NW_, MT, WF, W>;                                                       \
     __shared__ __align__(16) uint8_t st0[S::kStage], st1[S::kStage];                           \
     __shared__ __align__(16) uint16_t xs[S::XB * S::kXs / 2];                                  \
     __shared__ uint16_t list[APEX_MAX_PAIRS];                                                  \
@@ -502,7 +500,7 @@ __device__ __forceinline__ const float *row_scales(const typename WF::T *slot, i
 // SU == 1: hb[pair, i] = bf16(silu(W1[i] . x_b) * (W3[i] . x_b)), ungated.
 // SU  > 1: uv[(2z) * P*I + pair*I + i] = W1[i] . x_b over the split, uv[(2z+1) ...] = W3.
 // E4M3 slots: the dot products are multiplied by the rows' scales.
-template <int MT, int SU, class WF>
+template <int MT, int SU, class WF, bool W>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void up_gemm(
     const float *__restrict__ x, int d, int I, int P, int k, const int32_t *__restrict__ exec_idx,
     const int32_t *__restrict__ slot_of_expert, int n_slots,
@@ -517,9 +515,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     const int i0 = blockIdx.x * kRows;
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const typename WF::T *slot = slots + size_t(s) * slot_stride;
-    const uint8_t *W = reinterpret_cast<const uint8_t *>(slot + size_t(i0) * 2 * d / WF::kKPerElem);
+    const uint8_t *w1 = reinterpret_cast<const uint8_t *>(slot + size_t(i0) * 2 * d / WF::kKPerElem);
     const size_t row_bytes = size_t(d) / WF::kKPerElem * sizeof(typename WF::T);
-    const uint8_t *const wbase[2] = {W, W + row_bytes};
+    const uint8_t *const wbase[2] = {w1, w1 + row_bytes};
     const size_t wstride = 2 * row_bytes;
     // MXFP4 block scales of W1 and W3 rows i0.. (unused by the other formats)
     const uint8_t *sc = reinterpret_cast<const uint8_t *>(slot) + size_t(3) * I * d / 2;
@@ -533,7 +531,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     const auto pass = [&](auto tiles, int t0) {
         constexpr int NT = decltype(tiles)::value;
         floatx4 acc[2][NT];
-        gemm_tile<2, MT, NT, ActF32, WF>(stage, xs, t0 == 0, wbase, wstride, sbase, size_t(d / 32),
+        gemm_tile<2, MT, NT, W, ActF32, WF>(stage, xs, t0 == 0, wbase, wstride, sbase, size_t(d / 32),
                                          I - i0, d, kr, list + t0, n_e - t0, k, x,
                                          size_t(d) * sizeof(float), acc);
         const int i = i0 + 16 * wave + (lane & 15);
@@ -572,7 +570,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 // down_gemm: grid (ceil(d / 64), E, SD).  64 rows j of W2 of expert blockIdx.y, K (= I)
 // blocks of split blockIdx.z.  yp[z * P*d + pair*d + j] = W2[j] . h[pair] over the split.
 // The activations are the bf16 h rows.
-template <int MT, class WF>
+template <int MT, class WF, bool W>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void down_gemm(
     int d, int I, int P, const int32_t *__restrict__ exec_idx,
     const int32_t *__restrict__ slot_of_expert, int n_slots,
@@ -601,7 +599,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     const auto pass = [&](auto tiles, int t0) {
         constexpr int NT = decltype(tiles)::value;
         floatx4 acc[1][NT];
-        gemm_tile<1, MT, NT, ActBf16, WF>(stage, xs, t0 == 0, wbase, wstride, sbase,
+        gemm_tile<1, MT, NT, W, ActBf16, WF>(stage, xs, t0 == 0, wbase, wstride, sbase,
                                           size_t(I / 32), d - j0, I, kr, list + t0, n_e - t0, 1,
                                           hb, size_t(I) * sizeof(__bf16), acc);
         const int j = j0 + 16 * wave + (lane & 15);
@@ -725,13 +723,13 @@ struct Plan {
 // The launch plan for weight format WF.  The split rules were fitted to timings of
 // every split pair (1-4 each) on grouped calls of the Granite-3B, OLMoE, Mixtral,
 // DeepSeek-16B and Phi-7B expert shapes in all three formats (24 to 64 resident
-// experts): each K split adds a prologue (finding the expert's pairs, the first load)
-// and partial sums, and pays only when the projection has too few workgroups to keep
-// HBM busy.  The gate/up target grows with the per-byte cost of widening the codes
-// (bf16 none, E4M3 most per byte); the down projection splits only over long K (for
-// Mixtral's I = 14336).  The rule is within 1 % of the best split pair on average over
-// those calls (the earlier rule, a common 1024-workgroup target with two K blocks per
-// split, was 7 % off, and up to 25 % on OLMoE B64 with E4M3 experts).
+// experts), on an earlier loop that took the weights through registers; they have not been
+// fitted again, so that the order of the sums stays as it was.  Each K split adds a
+// prologue (finding the expert's pairs, the first load) and partial sums, and pays only
+// when the projection has too few workgroups to keep HBM busy.  The gate/up target grows
+// with the per-byte cost of widening the codes (bf16 none, E4M3 most per byte); the down
+// projection splits only over long K (for Mixtral's I = 14336).  On that loop the rule was
+// within 1 % of the best split pair on average over those calls.
 template <class WF>
 Plan plan_for(int B, int d, int I, int k, int E, int n_slots) {
     Plan pl;
@@ -763,9 +761,8 @@ Plan plan_for(int B, int d, int I, int k, int E, int n_slots) {
 // stages, so two workgroups a CU: 68.2), all resident 142.8 -> 130.0; Mixtral 4 of 8, 32 tokens
 // E4M3 143.5 -> 132.8; OLMoE 24, 8 tokens MXFP4 43.6 -> 35.6.  Over 221 shapes 1.02 as a mean,
 // 0.93 to 1.25.
-template <int NW, int MT, class WF>
+template <class S>
 size_t lds_pad(dim3 g, int experts) {
-    using S = TileShape<NW, MT, WF>;
     const int n = int(g.x * g.z) * experts, most = std::min(160 * 1024 / S::lds(S::XB), 8);
     if (n > 1024) return 0;
     int per = most, best = INT_MAX;
@@ -776,34 +773,70 @@ size_t lds_pad(dim3 g, int experts) {
     return per == most ? 0 : std::max(0, 160 * 1024 / (per + 1) + 1024 - S::lds(S::XB));
 }
 
-template <int MT, int SU, class WF>
-void launch_up(dim3 g, int experts, hipStream_t st, const float *x, int d, int I, int P, int k,
-               const int32_t *exec_idx, const int32_t *soe, int n_slots,
-               const typename WF::T *slots, size_t stride, __bf16 *hb, float *uv) {
-    hipLaunchKernelGGL((up_gemm<MT, SU, WF>), g, dim3(kThreads), (lds_pad<2, MT, WF>(g, experts)), st, x, d, I, P, k, exec_idx,
-                       soe, n_slots, slots, stride, hb, uv);
+// Whether a launch with K splits of `units` units takes blocks of two lines per row.  bf16:
+// always but for gate/up of 48 tokens and more, where two stages of them would leave no room
+// for a second workgroup (down with one line: 24 to 47 tokens 0.93 of the speed, 48 and more
+// 0.94, 16 0.91, gate/up 0.93).  MXFP4: never (down up to 23 tokens 0.96 with two).  E4M3: up to
+// 23 tokens (more have one line as their unit), unless a split is short and the launch large,
+// where the workgroups that two lines leave no room for count for more: Granite-3B, 16 tokens,
+// all 40 experts 35.6 us a call with two lines, 28.6 with one, but Mixtral, 4 tokens, 126 and
+// 142, 64 experts of 3952 x 1808, 10 tokens, 153 and 188.  Figures: means over shapes drawn from 256
+// to 4096 x 14336 with 4 to 64 experts.
+template <int NW, int MT, class WF>
+bool wide_rows(dim3 g, int experts, int units) {
+    if (WF::kChunkK == 8) return NW == 1 || MT <= 2;
+    if (WF::kChunkK == 32 || MT > 1) return false;
+    return units > 4 || int(g.x * g.z) * experts <= 512;
+}
+// Which of the two a format and tile count can take at all.
+template <int NW, int MT, class WF, bool W>
+constexpr bool has_rows() {
+    if (WF::kChunkK == 16 && MT == 1) return true;
+    return W == (WF::kChunkK == 8 && (NW == 1 || MT <= 2));
 }
 
-template <int MT, class WF>
-void launch_up_splits(int SU, dim3 g, int experts, hipStream_t st, const float *x, int d, int I, int P, int k,
-                      const int32_t *exec_idx, const int32_t *soe, int n_slots,
-                      const typename WF::T *slots, size_t stride, __bf16 *hb, float *uv) {
-    if (SU == 1)
-        launch_up<MT, 1, WF>(g, experts, st, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
-    else if (SU == 2)
-        launch_up<MT, 2, WF>(g, experts, st, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
-    else if (SU == 3)
-        launch_up<MT, 3, WF>(g, experts, st, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
+template <int MT, int SU, class WF, bool W, class... A>
+void launch_up(dim3 g, int experts, hipStream_t st, A... a) {
+    if constexpr (has_rows<2, MT, WF, W>())
+        hipLaunchKernelGGL((up_gemm<MT, SU, WF, W>), g, dim3(kThreads),
+                           (lds_pad<TileShape<2, MT, WF, W>>(g, experts)), st, a...);
+}
+
+template <int MT, class WF, bool W, class... A>
+void launch_up_splits(dim3 g, int experts, hipStream_t st, A... a) {
+    if (g.z == 1)
+        launch_up<MT, 1, WF, W>(g, experts, st, a...);
+    else if (g.z == 2)
+        launch_up<MT, 2, WF, W>(g, experts, st, a...);
+    else if (g.z == 3)
+        launch_up<MT, 3, WF, W>(g, experts, st, a...);
     else
-        launch_up<MT, 4, WF>(g, experts, st, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
+        launch_up<MT, 4, WF, W>(g, experts, st, a...);
 }
 
-template <int MT, class WF>
-void launch_down(dim3 g, int experts, hipStream_t st, int d, int I, int P, const int32_t *exec_idx,
-                 const int32_t *soe, int n_slots, const typename WF::T *slots, size_t stride,
-                 const __bf16 *hb, float *yp) {
-    hipLaunchKernelGGL((down_gemm<MT, WF>), g, dim3(kThreads), (lds_pad<1, MT, WF>(g, experts)), st, d, I, P, exec_idx, soe,
-                       n_slots, slots, stride, hb, yp);
+template <int MT, class WF, bool W, class... A>
+void launch_down(dim3 g, int experts, hipStream_t st, A... a) {
+    if constexpr (has_rows<1, MT, WF, W>())
+        hipLaunchKernelGGL((down_gemm<MT, WF, W>), g, dim3(kThreads),
+                           (lds_pad<TileShape<1, MT, WF, W>>(g, experts)), st, a...);
+}
+
+// The gate/up and the down launch for MT token tiles per pass.
+template <int MT, class WF, class... A>
+void run_up(dim3 g, int experts, int K, hipStream_t st, A... a) {
+    const int unit = WF::template plan_kb<MT>() * int(g.z), units = (K + unit - 1) / unit;
+    if (wide_rows<2, MT, WF>(g, experts, units))
+        launch_up_splits<MT, WF, true>(g, experts, st, a...);
+    else
+        launch_up_splits<MT, WF, false>(g, experts, st, a...);
+}
+template <int MT, class WF, class... A>
+void run_down(dim3 g, int experts, int K, hipStream_t st, A... a) {
+    const int unit = WF::template plan_kb<MT>() * int(g.z), units = (K + unit - 1) / unit;
+    if (wide_rows<1, MT, WF>(g, experts, units))
+        launch_down<MT, WF, true>(g, experts, st, a...);
+    else
+        launch_down<MT, WF, false>(g, experts, st, a...);
 }
 
 // The launches of one call for slots of weight format WF.
@@ -820,14 +853,11 @@ apex_status run_grouped(const float *x, int B, int d, int I, int E, int k,
     float *yp = reinterpret_cast<float *>(wsb + apex::align_up(pl.h_bytes, 256));
     const dim3 gu((I + kRows - 1) / kRows, E, pl.SU);
     if (pl.MT == 4)
-        launch_up_splits<4, WF>(pl.SU, gu, experts, stream, x, d, I, P, k, exec_idx, soe, n_slots, slots,
-                                stride, hb, uv);
+        run_up<4, WF>(gu, experts, d, stream, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
     else if (pl.MT == 2)
-        launch_up_splits<2, WF>(pl.SU, gu, experts, stream, x, d, I, P, k, exec_idx, soe, n_slots, slots,
-                                stride, hb, uv);
+        run_up<2, WF>(gu, experts, d, stream, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
     else
-        launch_up_splits<1, WF>(pl.SU, gu, experts, stream, x, d, I, P, k, exec_idx, soe, n_slots, slots,
-                                stride, hb, uv);
+        run_up<1, WF>(gu, experts, d, stream, x, d, I, P, k, exec_idx, soe, n_slots, slots, stride, hb, uv);
     APEX_HIP(hipGetLastError());
     if (pl.SU > 1) {
         const dim3 gr((P * (I / 8) + kThreads - 1) / kThreads);
@@ -844,12 +874,13 @@ apex_status run_grouped(const float *x, int B, int d, int I, int E, int k,
     }
 
     const dim3 gd((d + kRows - 1) / kRows, E, pl.SD);
+    const __bf16 *hbc = hb;
     if (pl.MT == 4)
-        launch_down<4, WF>(gd, experts, stream, d, I, P, exec_idx, soe, n_slots, slots, stride, hb, yp);
+        run_down<4, WF>(gd, experts, I, stream, d, I, P, exec_idx, soe, n_slots, slots, stride, hbc, yp);
     else if (pl.MT == 2)
-        launch_down<2, WF>(gd, experts, stream, d, I, P, exec_idx, soe, n_slots, slots, stride, hb, yp);
+        run_down<2, WF>(gd, experts, I, stream, d, I, P, exec_idx, soe, n_slots, slots, stride, hbc, yp);
     else
-        launch_down<1, WF>(gd, experts, stream, d, I, P, exec_idx, soe, n_slots, slots, stride, hb, yp);
+        run_down<1, WF>(gd, experts, I, stream, d, I, P, exec_idx, soe, n_slots, slots, stride, hbc, yp);
     APEX_HIP(hipGetLastError());
     const dim3 gc((d / 4 + kThreads - 1) / kThreads, B);
     if (pl.SD == 1)

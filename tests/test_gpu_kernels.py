@@ -477,6 +477,8 @@ FP8_SHAPES = [
     (shape("fp8_split_a", 431, 784, 4, 2, I=1008), 4),     # few experts, ragged K tails
     (shape("fp8_split_b", 432, 1008, 4, 2, I=784), 5),
     (shape("fp8_small", 433, 16, 3, 2, I=48), 3),          # one 16-byte chunk per row
+    # short ragged rows and more than 512 workgroups in both projections: blocks of one line
+    (shape("fp8_short_rows", 439, 560, 64, 8, I=592), 20),
     # one token, rows of 1025..4096 values: the up projection splits each row over a
     # workgroup (one 16-code chunk per lane, 1, 2 or 4 row pairs per workgroup)
     (configs.PHI_7B, 1), (configs.DEEPSEEK_16B, 1),
