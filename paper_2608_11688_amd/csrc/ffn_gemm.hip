@@ -246,8 +246,8 @@ __device__ __forceinline__ uint4 widen8(WMxfp4, uint4 v, int j, float sc) {
 // workgroup more, up to four (32 tokens MXFP4 1.06 as a mean, 64 tokens E4M3 1.04, Granite-3B
 // 16 tokens bf16 1.07).
 // Calls of 221 shapes (2 to 64 tokens, six models with all or some experts resident, three
-// formats) against the loop through registers with two barriers a block: 1.11 as a mean,
-// 0.94 to 1.58.
+// formats) against the loop through registers with two barriers a block: 1.12 as a mean,
+// 0.95 (DeepSeek-16B, 24 experts, 2 and 4 tokens MXFP4) to 1.57.
 template <int NW, int MT, class WF, bool W>
 struct TileShape {
     static constexpr int kRowBytes = W ? 256 : 128;   // of a weight row per block
@@ -759,8 +759,8 @@ Plan plan_for(int B, int d, int I, int k, int E, int n_slots) {
 // load a block and leave, and would hold up the others.
 // us a call, without -> with: OLMoE, 24 experts of 64 resident, 64 tokens bf16 77.8 -> 65.4 (three
 // stages, so two workgroups a CU: 68.2), all resident 142.8 -> 130.0; Mixtral 4 of 8, 32 tokens
-// E4M3 143.5 -> 132.8; OLMoE 24, 8 tokens MXFP4 43.6 -> 35.6.  Over 221 shapes 1.02 as a mean,
-// 0.93 to 1.25.
+// E4M3 143.5 -> 132.8; OLMoE 24, 8 tokens MXFP4 36.6 -> 29.8.  Over 221 shapes 1.02 as a mean,
+// 0.92 (OLMoE 24, 16 tokens E4M3) to 1.23.
 template <class S>
 size_t lds_pad(dim3 g, int experts) {
     const int n = int(g.x * g.z) * experts, most = std::min(160 * 1024 / S::lds(S::XB), 8);
@@ -775,12 +775,13 @@ size_t lds_pad(dim3 g, int experts) {
 
 // Whether a launch with K splits of `units` units takes blocks of two lines per row.  bf16:
 // always but for gate/up of 48 tokens and more, where two stages of them would leave no room
-// for a second workgroup (down with one line: 24 to 47 tokens 0.93 of the speed, 48 and more
-// 0.94, 16 0.91, gate/up 0.93).  MXFP4: never (down up to 23 tokens 0.96 with two).  E4M3: up to
+// for a second workgroup (with one line the speed is: down up to 23 tokens 0.91, 24 to 47 0.93,
+// 48 and more 0.94, gate/up 0.93).  MXFP4: never (down up to 23 tokens with two: 1.01 over drawn
+// shapes, but 0.95 at those of six models).  E4M3: up to
 // 23 tokens (more have one line as their unit), unless a split is short and the launch large,
 // where the workgroups that two lines leave no room for count for more: Granite-3B, 16 tokens,
-// all 40 experts 35.6 us a call with two lines, 28.6 with one, but Mixtral, 4 tokens, 126 and
-// 142, 64 experts of 3952 x 1808, 10 tokens, 153 and 188.  Figures: means over shapes drawn from 256
+// all 40 experts 35.6 us a call with two lines, 28.7 with one, but Mixtral, 4 tokens, 121 and
+// 136, 64 experts of 3952 x 1808, 10 tokens, 153 and 188.  Figures: means over shapes drawn from 256
 // to 4096 x 14336 with 4 to 64 experts.
 template <int NW, int MT, class WF>
 bool wide_rows(dim3 g, int experts, int units) {
