@@ -773,6 +773,13 @@ size_t lds_pad(dim3 g, int experts) {
     return per == most ? 0 : std::max(0, 160 * 1024 / (per + 1) + 1024 - S::lds(S::XB));
 }
 
+// Which of one and two lines per row (W) a projection, tile count and format has kernels for.
+template <int NW, int MT, class WF, bool W>
+constexpr bool has_rows() {
+    if (WF::kChunkK == 16 && MT == 1) return true;
+    return W == (WF::kChunkK == 8 && (NW == 1 || MT <= 2));
+}
+
 // Whether a launch with K splits of `units` units takes blocks of two lines per row.  bf16:
 // always but for gate/up of 48 tokens and more, where two stages of them would leave no room
 // for a second workgroup (with one line the speed is: down up to 23 tokens 0.91, 24 to 47 0.93,
@@ -785,17 +792,10 @@ size_t lds_pad(dim3 g, int experts) {
 // to 4096 x 14336 with 4 to 64 experts.
 template <int NW, int MT, class WF>
 bool wide_rows(dim3 g, int experts, int units) {
-    if (WF::kChunkK == 8) return NW == 1 || MT <= 2;
-    if (WF::kChunkK == 32 || MT > 1) return false;
+    if (!has_rows<NW, MT, WF, true>()) return false;
+    if (!has_rows<NW, MT, WF, false>()) return true;
     return units > 4 || int(g.x * g.z) * experts <= 512;
 }
-// Which of the two a format and tile count can take at all.
-template <int NW, int MT, class WF, bool W>
-constexpr bool has_rows() {
-    if (WF::kChunkK == 16 && MT == 1) return true;
-    return W == (WF::kChunkK == 8 && (NW == 1 || MT <= 2));
-}
-
 template <int MT, int SU, class WF, bool W, class... A>
 void launch_up(dim3 g, int experts, hipStream_t st, A... a) {
     if constexpr (has_rows<2, MT, WF, W>())
